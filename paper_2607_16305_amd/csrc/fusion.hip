@@ -39,7 +39,6 @@ hipError_t launch_fusion(int dt, const FusionFfn& f, int layers, int64_t n, int6
   g1.b_batch = (int64_t)f.d_ff * g1.k_bytes;
   g1.out_batch = n_keep * (int64_t)f.d_ff * es;
   g1.cols = f.d_ff;
-  g1.ksplit = (int)(g1.k_bytes / TG_KB);
   g1.tiles = (int)(rt * ((f.d_ff + TgShape::BN / 2 - 1) / (TgShape::BN / 2)));
   g1.count = count;
   g1.count_step = kept_batch != 0 ? 1 : 0;
@@ -60,7 +59,6 @@ hipError_t launch_fusion(int dt, const FusionFfn& f, int layers, int64_t n, int6
   g2.kept_batch = kept_batch;
   g2.out_ld = (int64_t)f.d_h * es;
   g2.cols = f.d_h;
-  g2.ksplit = (int)(g2.k_bytes / TG_KB);
   g2.tiles = (int)(rt * ((f.d_h + TgShape::BN - 1) / TgShape::BN));
   g2.count = count;
   g2.count_step = g1.count_step;
@@ -83,7 +81,6 @@ hipError_t launch_propagate(int dt, const void* w_p_t, int steps, int64_t n_keep
     g.a_bytes = (int64_t)d_v * es;
     g.k_bytes = g.a_bytes;
     g.cols = d_v;
-    g.ksplit = (int)(g.k_bytes / TG_KB);
     g.tiles = (int)(rt * ((d_v + TgShape::BN - 1) / TgShape::BN));
     g.count = count;
     g.count_step = 0;

@@ -143,12 +143,10 @@ hipError_t launch_multiscale(int dt, int scales, int64_t n, int64_t n_keep, cons
                                     d_v, k, r, st, 0, Sm, count);
   if (e != hipSuccess) return e;
 
-  // q = round(H[kept] W_he): every K stage of an A row comes from the kept
-  // token's hidden row (a1 gathered by sel = kept)
+  // q = round(H[kept] W_he)
   TileGemmParams g{};
   g.a0 = static_cast<const char*>(hidden);
-  g.a1 = static_cast<const char*>(hidden);
-  g.sel = kept;
+  g.a_sel = kept;
   g.sel_rows = (int)n;
   g.b = static_cast<const char*>(w_he_t);
   g.out = static_cast<char*>(q);
@@ -156,7 +154,6 @@ hipError_t launch_multiscale(int dt, int scales, int64_t n, int64_t n_keep, cons
   g.a_bytes = (int64_t)d_h * es;
   g.k_bytes = g.a_bytes;
   g.cols = d_v;
-  g.ksplit = 0;
   g.count = count;   // a counted list: rows past count[0] are skipped
   g.count_step = 0;
   g.tiles = (int)(((n_keep + TgShape::BM - 1) / TgShape::BM) *

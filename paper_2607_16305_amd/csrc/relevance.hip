@@ -895,7 +895,6 @@ hipError_t launch_relevance_table(int dt, const void* scene_keys, const Relevanc
   g.a_bytes = (int64_t)d_e * es;
   g.k_bytes = g.a_bytes;
   g.cols = mlp.hidden;
-  g.ksplit = (int)(g.a_bytes / TG_KB);
   g.tiles = (int)(((S + TgShape::BM - 1) / TgShape::BM) *
                   ((mlp.hidden + TgShape::BN - 1) / TgShape::BN));
   return launch_tile_gemm<EPI_LOGIT>(dt, g, 1, st);
@@ -923,7 +922,6 @@ hipError_t launch_relevance(int dt, const void* q, const int32_t* scene, const f
   g1.k_bytes = g1.a_bytes;
   g1.sel_rows = S;
   g1.cols = mlp.hidden;
-  g1.ksplit = (int)(g1.a_bytes / TG_KB);
   g1.tiles = (int)(rt * ((mlp.hidden + TgShape::BN - 1) / TgShape::BN));
   hipError_t e = launch_tile_gemm<EPI_ACT_TAB>(dt, g1, 1, st);
   if (e != hipSuccess) return e;
@@ -972,13 +970,8 @@ hipError_t launch_relevance(int dt, const void* q, const int32_t* scene, const f
   g2.a_bytes = (int64_t)mlp.hidden * es;
   g2.k_bytes = g2.a_bytes;
   g2.cols = P;
-  g2.ksplit = (int)(g2.k_bytes / TG_KB);
   g2.tiles = (int)(rt * ((P + TgShape::BN - 1) / TgShape::BN));
-  // large products on the projection's 256 x 256 tiles, small ones here
-  if (!launch_logits_gemm(dt, act, mlp.w2, mlp.b2, logits, rows, P, g2.k_bytes, st))
-    e = launch_tile_gemm<EPI_LOGIT>(dt, g2, 1, st);
-  else
-    e = hipGetLastError();
+  e = launch_tile_gemm<EPI_LOGIT>(dt, g2, 1, st);
   if (e != hipSuccess) return e;
   const dim3 wgrid((unsigned)((rows + 3) / 4));
   if (k <= 4)

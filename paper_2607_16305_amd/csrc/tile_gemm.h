@@ -23,34 +23,35 @@
 //   EPI_ACT_TAB C + tab[sel[row]] (a float32 row of [sel_rows, cols]: the
 //               relevance MLP's per-scene half of the first layer, b1
 //               included), ReLU, one rounding, [rows, cols].
+//   EPI_Q       round(C), column c of row r at q[c / d_e][r][c % d_e] (the
+//               query projection of all layers).
 //
-// An A row may take its first `ksplit` stages from a0 and the rest from a
-// gathered row of a1 (the relevance MLP's [query ; scene key] input).
+// With a_sel, row r of A is row a_sel[r] of a0 (the multi-scale router's
+// queries: the kept tokens' hidden rows).
+//
+// Products with enough large tiles to fill the chip run on the phased kernel
+// (phase_gemm.h); see launch_tile_gemm.
 
 #pragma once
 
 #include "common.h"
 #include "dtl.h"
+#include "phase_gemm.h"
 
 namespace lookme {
 
-// BIG: 128 x 128 output tiles (each wave 4 x 4 MFMA tiles), for products with
-// enough rows to fill the chip with them (the relevance MLP's first layer of
-// large batches): a quarter of the tiles, half the operand bytes into LDS.
-template <bool BIG>
-using TgShapeT = DtlShape<2, 2, BIG ? 4 : 2, BIG ? 4 : 2, 128>;
-using TgShape = TgShapeT<false>;
+using TgShape = DtlShape<2, 2, 2, 2, 128>;
 constexpr int TG_KB = 128;
 
 enum : int {
   EPI_ACT = 0, EPI_LOGIT = 1, EPI_SWIGLU = 2, EPI_RESID = 3, EPI_ADD = 4, EPI_STORE = 5,
-  EPI_ACT_TAB = 6
+  EPI_ACT_TAB = 6, EPI_Q = 7
 };
 
 struct TileGemmParams {
-  const char* a0;           // [rows, K] (or the first ksplit stages of a row)
-  const char* a1;           // gathered second part of A rows, or null
-  const int32_t* sel;       // [rows] row of a1 for each A row (clamped to [0, sel_rows))
+  const char* a0;           // [rows, K]
+  const int32_t* a_sel;     // or null: [rows] row of a0 for each A row (clamped to [0, sel_rows))
+  const int32_t* sel;       // EPI_ACT_TAB: [rows] row of tab (clamped to [0, sel_rows))
   const char* b;            // [cols, K] (EPI_SWIGLU: gate rows)
   const char* b2;           // EPI_SWIGLU: up rows [cols, K]
   const float* bias;        // [cols] or null (EPI_ACT, EPI_LOGIT)
@@ -61,25 +62,26 @@ struct TileGemmParams {
   const int32_t* count;     // or null: batch z uses only its first count[z * count_step]
                             // rows (a gate's counted kept list); tiles past them end at once
   int64_t rows;
-  int64_t a_bytes;          // bytes of an A row (of each part, when split)
+  int64_t a_bytes;          // bytes between A rows
   int64_t k_bytes;          // K in bytes, a multiple of 128
   int64_t b_ld;             // bytes between B rows (0: k_bytes; a column slice of a wider B)
   int64_t a_batch, b_batch, out_batch;   // byte strides between batches
   int64_t n, kept_batch;    // EPI_RESID: tokens per layer, stride of the kept lists
   int64_t out_ld;           // EPI_RESID: bytes of an H row
-  int sel_rows, cols, ksplit, tiles;
+  int sel_rows, cols, tiles;
   int col_major;            // tile ids run down the row tiles of a column block first
   int count_step;           // 1: a count per batch, 0: one count for all
+  int batches;              // phased kernel: number of batches
+  int d_e;                  // EPI_Q: columns of a layer (a multiple of 8)
 };
 
 // Origin of tile `tile`: row tiles of one column block are consecutive ids
 // when col_major (so they land on one XCD and share its L2 copy of the B
 // rows, which the larger operand then crosses HBM once), else the column
 // tiles of one row block.
-template <bool BIG = false>
 __device__ __forceinline__ void tile_origin(const TileGemmParams& a, int tile, int tcols,
                                             int64_t* m0, int* n0) {
-  constexpr int BM = TgShapeT<BIG>::BM;
+  constexpr int BM = TgShape::BM;
   if (a.col_major) {
     const int tiles_m = (int)((a.rows + BM - 1) / BM);
     *m0 = (int64_t)(tile % tiles_m) * BM;
@@ -95,15 +97,14 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.f + expf(-x)); 
 
 // Epilogue of a tile (tile index `tile` of batch z) from the accumulators of
 // thread tid: the lane holds rows m0 + wm + 16 i + 4 g + r and tile columns
-// wn + 16 j + n16.  xch: 4096 floats of LDS (EPI_SWIGLU only, small tiles).
-template <int DT, int EPI, bool BIG = false>
+// wn + 16 j + n16.  xch: 4096 floats of LDS (EPI_SWIGLU only).
+template <int DT, int EPI>
 __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
-                                              f32x4_t (&acc)[BIG ? 4 : 2][BIG ? 4 : 2],
+                                              f32x4_t (&acc)[2][2],
                                               int64_t z, int tile, int tid, float* xch,
                                               int64_t rows) {
-  using S = TgShapeT<BIG>;
-  constexpr int MI = BIG ? 4 : 2, NJ = BIG ? 4 : 2, WN = 2;
-  static_assert(!BIG || EPI != EPI_SWIGLU, "the SwiGLU exchange is laid out for small tiles");
+  using S = TgShape;
+  constexpr int MI = 2, NJ = 2, WN = 2;
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
   constexpr int TCOLS = EPI == EPI_SWIGLU ? S::BN / 2 : S::BN;
   const int lane = tid & 63, wv = tid >> 6;
@@ -111,105 +112,7 @@ __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
   const int wm = (wv / WN) * 16 * MI, wn = (wv % WN) * 16 * NJ;
   int64_t m0;
   int n0;
-  tile_origin<BIG>(a, tile, TCOLS, &m0, &n0);
-  if constexpr (BIG && EPI == EPI_ACT_TAB) {
-    if (a.cols % 8 == 0 &&
-        ((reinterpret_cast<uintptr_t>(a.out) | reinterpret_cast<uintptr_t>(a.tab)) & 15) == 0) {
-      // through LDS, 64 rows at a time (xch: the stage ring, free once every
-      // wave is past its last loads): the waves of those rows write their
-      // sums, then every thread takes 8-column pieces of a row, whose table
-      // part and output are 16-byte loads and stores (the lane layout of the
-      // accumulators gave 2-byte stores and 4-byte table loads, ~25 us of
-      // the Zipf batch's ~57)
-      constexpr int LD = S::BN + 4;   // padded row: the four row groups of a write on distinct banks
-#pragma unroll 1
-      for (int half = 0; half < 2; ++half) {
-        __syncthreads();
-        if (wv / WN == half) {
-#pragma unroll
-          for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                xch[(16 * i + 4 * g + r) * LD + wn + 16 * j + n16] = acc[i][j][r];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 64 * S::BN / 8 / 256; ++c) {
-          const int id = tid + 256 * c;
-          const int lr = id / (S::BN / 8), cc = (id % (S::BN / 8)) * 8;
-          const int64_t row = m0 + 64 * half + lr;
-          const int col = n0 + cc;
-          if (row >= rows || col >= a.cols) continue;
-          int sc = a.sel[row];
-          sc = sc < 0 ? 0 : (sc >= a.sel_rows ? a.sel_rows - 1 : sc);
-          const f32x4_t* tp = reinterpret_cast<const f32x4_t*>(a.tab + (int64_t)sc * a.cols + col);
-          const f32x4_t t0 = tp[0], t1 = tp[1];
-          const f32x4_t* xp = reinterpret_cast<const f32x4_t*>(xch + lr * LD + cc);
-          const f32x4_t x0 = xp[0], x1 = xp[1];
-          float v[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = fmaxf(x0[e] + t0[e], 0.f);
-            v[4 + e] = fmaxf(x1[e] + t1[e], 0.f);
-          }
-          char* dst = a.out + (row * a.cols + col) * ES;
-          if constexpr (DT == DT_BF16) {
-            u32x4_t o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
-            *reinterpret_cast<u32x4_t*>(dst) = o;
-          } else {
-            *reinterpret_cast<f32x4_t*>(dst) = f32x4_t{v[0], v[1], v[2], v[3]};
-            *reinterpret_cast<f32x4_t*>(dst + 16) = f32x4_t{v[4], v[5], v[6], v[7]};
-          }
-        }
-      }
-      return;
-    }
-    // 32-bit row and table indices (rows of a product and scenes stay far
-    // below 2^31) keep the big tile's epilogue within the registers of two
-    // waves a SIMD; every table load still precedes the first store
-    int orow[MI][4], trow[MI][4];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t row = m0 + wm + 16 * i + 4 * g + r;
-        orow[i][r] = (int)(row < rows ? row : rows - 1);
-        const int sc = a.sel[orow[i][r]];
-        trow[i][r] = sc < 0 ? 0 : (sc >= a.sel_rows ? a.sel_rows - 1 : sc);
-      }
-    int col[NJ];
-    float old[NJ][MI][4];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      col[j] = n0 + wn + 16 * j + n16;
-      const int cc = col[j] < a.cols ? col[j] : a.cols - 1;
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) old[j][i][r] = a.tab[(int64_t)trow[i][r] * a.cols + cc];
-    }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      if (col[j] >= a.cols) continue;
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (m0 + wm + 16 * i + 4 * g + r >= rows) continue;
-          const float v = fmaxf(acc[i][j][r] + old[j][i][r], 0.f);
-          char* dst = a.out + ((int64_t)orow[i][r] * a.cols + col[j]) * ES;
-          if constexpr (DT == DT_BF16)
-            *reinterpret_cast<uint16_t*>(dst) = (uint16_t)f32_to_bf16_rne(v);
-          else
-            *reinterpret_cast<float*>(dst) = v;
-        }
-    }
-    return;
-  }
+  tile_origin(a, tile, TCOLS, &m0, &n0);
   if constexpr (EPI == EPI_SWIGLU) {
     // the up half (waves with wn = 32) passes its tile through LDS to the
     // gate half (wn = 0) of the same rows
@@ -319,6 +222,10 @@ __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
           if constexpr (EPI == EPI_ACT || EPI == EPI_STORE) {
             v = EPI == EPI_ACT ? fmaxf(c, 0.f) : c;
             dst = a.out + (orow[i][r] * a.cols + col[j]) * ES;
+          } else if constexpr (EPI == EPI_Q) {
+            v = c;
+            dst = a.out + (((int64_t)(col[j] / a.d_e) * a.rows + orow[i][r]) * a.d_e +
+                           col[j] % a.d_e) * ES;
           } else if constexpr (EPI == EPI_ACT_TAB) {
             v = fmaxf(c + old[j][i][r], 0.f);
             dst = a.out + (orow[i][r] * a.cols + col[j]) * ES;
@@ -338,13 +245,12 @@ __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
   }
 }
 
-template <int DT, int EPI, int NS, bool BIG = false>
-__global__ __launch_bounds__(256, BIG ? 2 : 1) void tile_gemm_kernel(TileGemmParams a) {
-  using S = TgShapeT<BIG>;
-  constexpr int MI = BIG ? 4 : 2, NJ = BIG ? 4 : 2, KB = TG_KB, KSL = KB / 64, WN = 2;
+template <int DT, int EPI, int NS>
+__global__ __launch_bounds__(256) void tile_gemm_kernel(TileGemmParams a) {
+  using S = TgShape;
+  constexpr int MI = 2, NJ = 2, KB = TG_KB, KSL = KB / 64, WN = 2;
   constexpr int TCOLS = EPI == EPI_SWIGLU ? S::BN / 2 : S::BN;   // output columns a tile
   static_assert(NS >= 2, "a stage in flight while one is multiplied");
-  static_assert(!BIG || NS * S::STAGE >= 64 * (S::BN + 4) * 4, "room for the epilogue's 64 rows");
   __shared__ __attribute__((aligned(1024))) char lds[NS][S::STAGE];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -357,7 +263,7 @@ __global__ __launch_bounds__(256, BIG ? 2 : 1) void tile_gemm_kernel(TileGemmPar
   if (tile < 0) return;
   int64_t m0;
   int n0;
-  tile_origin<BIG>(a, tile, TCOLS, &m0, &n0);
+  tile_origin(a, tile, TCOLS, &m0, &n0);
   int64_t rows = a.rows;   // live rows of this batch
   if (a.count != nullptr) {
     const int64_t c = a.count[z * a.count_step];
@@ -368,21 +274,17 @@ __global__ __launch_bounds__(256, BIG ? 2 : 1) void tile_gemm_kernel(TileGemmPar
   const char* A0 = a.a0 + z * a.a_batch;
   const char* B0 = a.b + z * a.b_batch;
 
-  // load b covers tile row trow (A rows first, then B rows); an A row takes
-  // its first ksplit stages from p0 and the rest from p1; a B row is
-  // contiguous.  Rows past the edge are clamped (their outputs are not
-  // stored).
-  const char* p0[S::PER_WAVE];
-  const char* p1[S::PER_WAVE];
-  int split_at[S::PER_WAVE];
-  int sel[S::PER_WAVE];   // gathered a1 rows, loaded together (one branch, no wait each)
-  if (a.a1 != nullptr) {
+  // load b covers tile row trow (A rows first, then B rows).  Rows past the
+  // edge are clamped (their outputs are not stored).
+  const char* src[S::PER_WAVE];
+  int sel[S::PER_WAVE];   // gathered rows, loaded together (one branch, no wait each)
+  if (a.a_sel != nullptr) {
 #pragma unroll
     for (int b = 0; b < S::PER_WAVE; ++b) {
       const int trow = (wv * S::PER_WAVE + b) * S::RPI + lane / S::LPR;
       int64_t r = m0 + (trow < S::BM ? trow : 0);
       r = r < rows ? r : rows - 1;
-      sel[b] = a.sel[r];
+      sel[b] = a.a_sel[r];
     }
   }
 #pragma unroll
@@ -392,15 +294,11 @@ __global__ __launch_bounds__(256, BIG ? 2 : 1) void tile_gemm_kernel(TileGemmPar
     if (trow < S::BM) {
       int64_t r = m0 + trow;
       r = r < rows ? r : rows - 1;
-      p0[b] = A0 + r * a.a_bytes + chunk * 16;
-      if (a.a1 != nullptr) {
-        int s = sel[b];
-        s = s < 0 ? 0 : (s >= a.sel_rows ? a.sel_rows - 1 : s);
-        p1[b] = a.a1 + (int64_t)s * a.a_bytes + chunk * 16;
-      } else {
-        p1[b] = p0[b] + (int64_t)a.ksplit * KB;
+      if (a.a_sel != nullptr) {
+        const int s = sel[b];
+        r = s < 0 ? 0 : (s >= a.sel_rows ? a.sel_rows - 1 : s);
       }
-      split_at[b] = a.ksplit;
+      src[b] = A0 + r * a.a_bytes + chunk * 16;
     } else {
       int c = trow - S::BM;
       const char* base = B0;
@@ -413,20 +311,15 @@ __global__ __launch_bounds__(256, BIG ? 2 : 1) void tile_gemm_kernel(TileGemmPar
       }
       int r = n0 + c;
       r = r < a.cols ? r : a.cols - 1;
-      p0[b] = base + (int64_t)r * (a.b_ld != 0 ? a.b_ld : a.k_bytes) + chunk * 16;
-      p1[b] = p0[b];
-      split_at[b] = nst;
+      src[b] = base + (int64_t)r * (a.b_ld != 0 ? a.b_ld : a.k_bytes) + chunk * 16;
     }
   }
   auto issue = [&](int i) {
     const int s = i < nst ? i : nst - 1;   // past the end: a harmless reload
     char* dst = lds[i % NS];
 #pragma unroll
-    for (int b = 0; b < S::PER_WAVE; ++b) {
-      const char* src = s < split_at[b] ? p0[b] + (int64_t)s * KB
-                                        : p1[b] + (int64_t)(s - split_at[b]) * KB;
-      load_lds16(src, dst + (wv * S::PER_WAVE + b) * 1024);
-    }
+    for (int b = 0; b < S::PER_WAVE; ++b)
+      load_lds16(src[b] + (int64_t)s * KB, dst + (wv * S::PER_WAVE + b) * 1024);
   };
 
   f32x4_t acc[MI][NJ];
@@ -463,7 +356,218 @@ __global__ __launch_bounds__(256, BIG ? 2 : 1) void tile_gemm_kernel(TileGemmPar
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into LDS outlives the wave
 
-  tile_epilogue<DT, EPI, BIG>(a, acc, z, tile, tid, reinterpret_cast<float*>(&lds[0][0]), rows);
+  tile_epilogue<DT, EPI>(a, acc, z, tile, tid, reinterpret_cast<float*>(&lds[0][0]), rows);
+}
+
+// ---------------------------------------------------------------------------
+// The phased kernel (phase_gemm.h)
+// ---------------------------------------------------------------------------
+// 256 x 256 tiles, one workgroup a CU, in rounds of 256; when the last round
+// would have at most 128 of them, each of these is cut into four 128 x 128
+// tiles (same launch, after the others): a round of such quarters takes
+// about a third of a whole tile's time, two of them still less than a round
+// of whole tiles that leaves half of the chip idle.  (2304 x 2048 x 2048 for
+// four layers, 288 tiles: 115 -> 85 us; 11520 x 1536 x 2048, 270: 100 -> 73.)
+constexpr int PH_ROUND = 256;
+struct PhasePlan {
+  int whole, cut;   // tiles computed whole (the first ones), tiles cut in four
+};
+__host__ __device__ inline PhasePlan phase_plan(int tiles) {
+  const int rem = tiles % PH_ROUND;
+  const int cut = rem <= PH_ROUND / 2 ? rem : 0;
+  return PhasePlan{tiles - cut, cut};
+}
+
+// One tile: rows from m0, output columns from n0 of batch z.  cols must be a
+// multiple of 8, so that a lane's W columns are all inside or all outside and
+// its 16-byte accesses are aligned.
+template <int DT, int EPI, int MI, int NJ>
+__device__ __forceinline__ void phase_tile(const TileGemmParams& a, char* lds, int64_t z,
+                                           int64_t rows, int64_t m0, int n0) {
+  using S = PgShape<MI, NJ>;
+  constexpr int ES = DT == DT_BF16 ? 2 : 4, W = S::W;
+  PgLoop<DT, MI, NJ> L(lds, threadIdx.x);
+  {
+    const char* A0 = a.a0 + z * a.a_batch;
+    const int64_t bld = a.b_ld != 0 ? a.b_ld : a.k_bytes;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int q = 0; q < S::PA; ++q) {
+        int64_t r = m0 + h * S::HM + L.a_row(q);
+        r = r < rows ? r : rows - 1;
+        if (a.a_sel != nullptr) {
+          const int s = a.a_sel[r];
+          r = s < 0 ? 0 : (s >= a.sel_rows ? a.sel_rows - 1 : s);
+        }
+        L.pa[h][q] = A0 + r * a.a_bytes + L.a_chunk(q) * 16;
+      }
+      const char* B = EPI == EPI_SWIGLU && h == 1 ? a.b2 : a.b;
+#pragma unroll
+      for (int q = 0; q < S::PB; ++q) {
+        int r = n0 + (EPI == EPI_SWIGLU ? 0 : h * S::HN) + L.b_row(q);
+        r = r < a.cols ? r : a.cols - 1;
+        L.pb[h][q] = B + z * a.b_batch + r * bld + L.b_chunk(q) * 16;
+      }
+    }
+  }
+  f32x4_t acc[2][2][MI][NJ];
+  L.run((int)(a.k_bytes / 128), acc);
+
+  constexpr int QJ = EPI == EPI_SWIGLU ? 1 : 2;
+  int col[QJ];
+#pragma unroll
+  for (int qj = 0; qj < QJ; ++qj) col[qj] = n0 + qj * S::HN + L.wc * 16 * NJ + W * L.g;
+  const char* R = EPI == EPI_RESID ? a.out : a.res;
+#pragma unroll
+  for (int qi = 0; qi < 2; ++qi) {
+    // every load of the half's rows before its first store: a store may alias
+    // a later load as far as the compiler knows
+    int64_t row[MI], orow[MI];
+    int trow[MI];
+    bool ok[MI];
+    float old[MI][QJ][W];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      row[i] = m0 + qi * S::HM + L.wr * 16 * MI + 16 * i + L.n16;
+      ok[i] = row[i] < rows;
+      orow[i] = ok[i] ? row[i] : rows - 1;
+      trow[i] = 0;
+      if constexpr (EPI == EPI_RESID) {
+        int64_t t = a.kept[z * a.kept_batch + orow[i]];
+        t = t < 0 ? 0 : (t >= a.n ? a.n - 1 : t);
+        orow[i] = z * a.n + t;
+      }
+      if constexpr (EPI == EPI_ACT_TAB) {
+        const int s = a.sel[orow[i]];
+        trow[i] = s < 0 ? 0 : (s >= a.sel_rows ? a.sel_rows - 1 : s);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int qj = 0; qj < QJ; ++qj) {
+        const int cc = col[qj] < a.cols ? col[qj] : a.cols - W;
+        if constexpr (EPI == EPI_RESID)
+          ld_cols<DT, W>(R + orow[i] * a.out_ld + (int64_t)cc * ES, old[i][qj]);
+        else if constexpr (EPI == EPI_ADD)
+          ld_cols<DT, W>(R + (orow[i] * a.cols + cc) * ES, old[i][qj]);
+        else if constexpr (EPI == EPI_ACT_TAB)
+          ld_cols<DT_F32, W>(reinterpret_cast<const char*>(a.tab + (int64_t)trow[i] * a.cols + cc),
+                             old[i][qj]);
+        else if constexpr (EPI == EPI_ACT || EPI == EPI_LOGIT)
+#pragma unroll
+          for (int e = 0; e < W; ++e) old[i][qj][e] = a.bias != nullptr ? a.bias[cc + e] : 0.f;
+        else
+#pragma unroll
+          for (int e = 0; e < W; ++e) old[i][qj][e] = 0.f;
+      }
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      if (!ok[i]) continue;
+#pragma unroll
+      for (int qj = 0; qj < QJ; ++qj) {
+        if (col[qj] >= a.cols) continue;
+        float v[W];
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+          const float c = acc[qi][qj][i][e >> 2][e & 3];
+          if constexpr (EPI == EPI_SWIGLU) v[e] = silu_f(c) * acc[qi][1][i][e >> 2][e & 3];
+          else if constexpr (EPI == EPI_ACT || EPI == EPI_ACT_TAB) v[e] = fmaxf(c + old[i][qj][e], 0.f);
+          else if constexpr (EPI == EPI_STORE || EPI == EPI_Q) v[e] = c;
+          else v[e] = old[i][qj][e] + c;
+        }
+        if constexpr (EPI == EPI_LOGIT)
+          st_cols<DT_F32, W>(a.out + (orow[i] * a.cols + col[qj]) * 4, v);
+        else if constexpr (EPI == EPI_Q)
+          st_cols<DT, W>(a.out + (((int64_t)(col[qj] / a.d_e) * a.rows + orow[i]) * a.d_e +
+                                  col[qj] % a.d_e) * ES, v);
+        else if constexpr (EPI == EPI_RESID)
+          st_cols<DT, W>(a.out + orow[i] * a.out_ld + (int64_t)col[qj] * ES, v);
+        else
+          st_cols<DT, W>(a.out + z * a.out_batch + (orow[i] * a.cols + col[qj]) * ES, v);
+      }
+    }
+  }
+}
+
+// Tiles are numbered batch by batch, inside a batch the column tiles of one
+// row block after another (column-major was slower at every shape measured:
+// 32768 x 512 x 4096 113 against 142 us), and dealt to the XCDs in contiguous
+// ranges; with counts only the live row blocks are numbered, so that every
+// XCD gets its share of them (numbered over all rows, a list that is half
+// full left half of the XCDs idle).
+template <int DT, int EPI>
+__global__ __launch_bounds__(512, 2) void phase_gemm_kernel(TileGemmParams a) {
+  using S = PgShape<4, 2>;
+  constexpr int TCOLS = EPI == EPI_SWIGLU ? S::HN : S::BN;
+  __shared__ __attribute__((aligned(1024))) char lds[2 * S::BUF];
+  const int tn = (a.cols + TCOLS - 1) / TCOLS;
+  auto live = [&](int z) -> int64_t {   // rows of batch z
+    if (a.count == nullptr) return a.rows;
+    const int64_t c = a.count[z * a.count_step];
+    return c < 0 ? 0 : (c < a.rows ? c : a.rows);
+  };
+  auto tiles_of = [&](int64_t rows) { return (int)((rows + S::BM - 1) / S::BM) * tn; };
+  int total = 0;
+  if (a.count == nullptr || a.count_step == 0) total = tiles_of(live(0)) * a.batches;
+  else
+    for (int z = 0; z < a.batches; ++z) total += tiles_of(live(z));
+  const PhasePlan pl = phase_plan(total);
+  const int first_cut = (pl.whole + 7) / 8 * 8;   // workgroups of the whole tiles
+  const bool whole = (int)blockIdx.x < first_cut;
+  int tile = whole ? xcd_remap(blockIdx.x, pl.whole)
+                   : xcd_remap((int)blockIdx.x - first_cut, 4 * pl.cut);
+  if (tile < 0) return;
+  const int quarter = tile & 3;
+  if (!whole) tile = pl.whole + (tile >> 2);
+  int z = 0;
+  int64_t rows = live(0);
+  if (a.count == nullptr || a.count_step == 0) {
+    const int per = tiles_of(rows);
+    z = tile / per;
+    tile -= z * per;
+  } else {
+    for (int per = tiles_of(rows); tile >= per; per = tiles_of(rows)) {
+      tile -= per;
+      rows = live(++z);
+    }
+  }
+  int64_t m0;
+  int n0;
+  m0 = (int64_t)(tile / tn) * S::BM;
+  n0 = (tile % tn) * TCOLS;
+  if (whole) {
+    phase_tile<DT, EPI, 4, 2>(a, lds, z, rows, m0, n0);
+  } else {
+    m0 += (quarter >> 1) * (S::BM / 2);
+    n0 += (quarter & 1) * (TCOLS / 2);
+    if (m0 < rows && n0 < a.cols) phase_tile<DT, EPI, 2, 1>(a, lds, z, rows, m0, n0);
+  }
+}
+
+template <int EPI>
+static int64_t phase_tiles(const TileGemmParams& p, int batches) {
+  using S = PgShape<4, 2>;
+  constexpr int TCOLS = EPI == EPI_SWIGLU ? S::HN : S::BN;
+  return (p.rows + S::BM - 1) / S::BM * ((p.cols + TCOLS - 1) / TCOLS) * batches;
+}
+
+template <int EPI>
+static hipError_t launch_phase(int dt, TileGemmParams p, int batches, hipStream_t st) {
+  const int64_t tiles = phase_tiles<EPI>(p, batches);
+  p.batches = batches;
+  const PhasePlan pl = phase_plan((int)tiles);
+  // with counts the number of tiles is the device's: any number up to `tiles`
+  // needs at most this many workgroups
+  const int64_t grid = p.count != nullptr ? tiles + 3 * (PH_ROUND / 2) + 8
+                                          : (pl.whole + 7) / 8 * 8 + 4 * pl.cut + 7;
+  const dim3 g((unsigned)((grid + 7) / 8 * 8));
+  if (dt == DT_BF16)
+    hipLaunchKernelGGL((phase_gemm_kernel<DT_BF16, EPI>), g, dim3(512), 0, st, p);
+  else
+    hipLaunchKernelGGL((phase_gemm_kernel<DT_F32, EPI>), g, dim3(512), 0, st, p);
+  return hipGetLastError();
 }
 
 // Launches the product over `batches` batches (blockIdx.y), tiles in the
@@ -475,24 +579,16 @@ template <int EPI>
 hipError_t launch_tile_gemm(int dt, TileGemmParams p, int batches, hipStream_t st) {
   // column-major tile order when B has at least as many rows as A
   p.col_major = (int64_t)p.cols * (EPI == EPI_SWIGLU ? 2 : 1) >= p.rows;
-  if constexpr (EPI == EPI_ACT_TAB) {
-    // 128 x 128 tiles once they alone fill two whole rounds of the CUs at
-    // two a CU (relevance first layer, Zipf batch: 1024 tiles, 51.0 -> 44.5
-    // us; the multi-scale batch's 720 took 37.4 against 35.4 us on 64 x 64)
-    constexpr int BB = TgShapeT<true>::BM;
-    const int64_t big = ((p.rows + BB - 1) / BB) * ((p.cols + BB - 1) / BB);
-    if (big * batches >= 1024) {
-      p.tiles = (int)big;
-      const unsigned gx = (unsigned)((p.tiles + 7) / 8 * 8);
-      const dim3 grid(gx, (unsigned)batches);
-      // two 32 KiB stages: two workgroups a CU
-      if (dt == DT_BF16)
-        hipLaunchKernelGGL((tile_gemm_kernel<DT_BF16, EPI, 2, true>), grid, dim3(256), 0, st, p);
-      else
-        hipLaunchKernelGGL((tile_gemm_kernel<DT_F32, EPI, 2, true>), grid, dim3(256), 0, st, p);
-      return hipGetLastError();
-    }
-  }
+  // The phased kernel from 48 tiles of 256 x 256 on (192 quarters): 2304 x
+  // 2048 x 2048 for four layers 310 -> 149 us (gate/up) and 147 -> 85 us
+  // (down), 512 x 2048 x 2048 for four layers (64 tiles) 31 -> 24.5 us;
+  // below it too few of the CUs get one: 1024 x 2048 x 2048 (32 tiles) 17.2
+  // us here, 18.0 phased, 512 x 2048 x 2048 13.2 and 16.5.  float32 is bound
+  // by the matrix cores on either, and 64 x 64 tiles fill the last round
+  // better: from 512 tiles on (16384 x 2048 x 1024 607 -> 561 us; 8192 x 1024
+  // x 1024, 128 tiles, 166 and 172).
+  if (p.cols % 8 == 0 && phase_tiles<EPI>(p, batches) >= (dt == DT_BF16 ? 48 : 512))
+    return launch_phase<EPI>(dt, p, batches, st);
   const unsigned gx = (unsigned)((p.tiles + 7) / 8 * 8);
   const dim3 grid(gx, (unsigned)batches);
   const int64_t wgs = (int64_t)gx * batches;
