@@ -152,6 +152,257 @@ __global__ __launch_bounds__(INJ_THREADS) void inject_kernel(
   }
 }
 
+// The multi-scale mix (Eq. 8) of one kept row j: the M scales' rows R^m (k
+// table rows each, weighted and rounded as the gather form writes them),
+// their products with the token's query, the softmax over the scales and the
+// weighted sum added into the token's hidden row.  The R^m stay in registers
+// between their two uses (C 16-byte chunks of each a thread): written to
+// memory by a gather launch and read back twice they were 210 MB on 11520
+// rows of two scales, and the two launches took 91 + 38.5 us (the whole gated
+// injection 237 -> 210 us).  Rows of more than 2 x 256
+// chunks (C = 0) gather twice instead.  Bound by the gather's traffic behind
+// the caches, like the injection above, so one workgroup a row and every
+// chunk load of a thread in flight together.
+constexpr int MS_THREADS = 256;
+
+template <int DT, int K>
+__device__ __forceinline__ u32x4_t weighted_chunk(const char* __restrict__ values,
+                                                  const int64_t (&vrow)[K], const float (&wt)[K],
+                                                  int k, int64_t v_bytes, int c) {
+  u32x4_t vv[K], out;
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+    if (i < k) vv[i] = ld16(values + vrow[i] * v_bytes + (int64_t)c * 16);
+  if constexpr (DT == DT_BF16) {
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      if (i < k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[2 * e] = fmaf(wt[i], bf16lo(vv[i][e]), acc[2 * e]);
+          acc[2 * e + 1] = fmaf(wt[i], bf16hi(vv[i][e]), acc[2 * e + 1]);
+        }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2(acc[2 * e], acc[2 * e + 1]);
+  } else {
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      if (i < k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(wt[i], as_f32(vv[i][e]), acc[e]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = as_u32(acc[e]);
+  }
+  return out;
+}
+
+template <int DT>
+__device__ __forceinline__ float chunk_dot(u32x4_t a, u32x4_t b, float acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (DT == DT_BF16) {
+      acc = fmaf(bf16lo(a[e]), bf16lo(b[e]), acc);
+      acc = fmaf(bf16hi(a[e]), bf16hi(b[e]), acc);
+    } else {
+      acc = fmaf(as_f32(a[e]), as_f32(b[e]), acc);
+    }
+  }
+  return acc;
+}
+
+// MM: scales compiled for (M <= MM).  A row whose token id is out of range is
+// left alone and counted once a scale; a scale whose scene or a primitive is
+// out of range has R^m = 0 and is counted.
+template <int DT, int K, int MM, int C>
+__global__ __launch_bounds__(MS_THREADS) void ms_mix_kernel(
+    int64_t n, const int32_t* __restrict__ kept, const int32_t* __restrict__ scene_all,
+    const int32_t* __restrict__ prim_all, const float* __restrict__ w_all,
+    const char* __restrict__ values, int Sm, int P, int k, int M, int64_t v_bytes,
+    const char* __restrict__ q, char* __restrict__ hidden, int64_t h_bytes, float inv_sqrt_d,
+    const int32_t* __restrict__ count) {
+  constexpr int CC = C > 0 ? C : 1;
+  __shared__ float red[MM][MS_THREADS / WAVE];
+  const int64_t j = blockIdx.x;
+  if (count != nullptr && j >= *count) return;   // past a counted list's end
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int nw = (int)(blockDim.x / WAVE);
+  const int64_t t = kept[j];
+  if (t < 0 || t >= n) {
+    if (tid == 0) atomicAdd(&g_index_errors, (unsigned long long)M);
+    return;
+  }
+  const int chunks = (int)(v_bytes / 16);
+  const char* qrow = q + j * v_bytes;
+
+  // scale m's table rows and weights (uniform over the workgroup); false:
+  // an index out of range
+  auto picks = [&](int m, int64_t (&vrow)[K], float (&wt)[K]) {
+    const int64_t row = (int64_t)m * n + t;
+    const int s = scene_all[row];
+    bool ok = s >= 0 && s < Sm;
+    const int64_t base = ((int64_t)m * Sm + (ok ? s : 0)) * P;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      vrow[i] = base;
+      wt[i] = 0.f;
+      if (i < k) {
+        const int p = prim_all[row * k + i];
+        const bool in = p >= 0 && p < P;
+        ok &= in;
+        vrow[i] = base + (in ? p : 0);
+        wt[i] = w_all[row * k + i];
+      }
+    }
+    return ok;
+  };
+
+  u32x4_t r[MM][CC];
+  float dot[MM];
+#pragma unroll
+  for (int m = 0; m < MM; ++m) {
+    dot[m] = 0.f;
+    if (m < M) {
+      int64_t vrow[K];
+      float wt[K];
+      const bool ok = picks(m, vrow, wt);
+      if (!ok && tid == 0) atomicAdd(&g_index_errors, 1ull);
+      if constexpr (C > 0) {
+#pragma unroll
+        for (int x = 0; x < CC; ++x) {
+          const int c = tid + x * (int)blockDim.x;
+          r[m][x] = u32x4_t{0, 0, 0, 0};
+          if (ok && c < chunks) {
+            r[m][x] = weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c);
+            dot[m] = chunk_dot<DT>(ld16(qrow + (int64_t)c * 16), r[m][x], dot[m]);
+          }
+        }
+      } else {
+        if (ok)
+          for (int c = tid; c < chunks; c += blockDim.x)
+            dot[m] = chunk_dot<DT>(ld16(qrow + (int64_t)c * 16),
+                                   weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c), dot[m]);
+      }
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < MM; ++m) {
+    if (m < M) {
+      float v = dot[m];
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+      if (lane == 0) red[m][wv] = v;
+    }
+  }
+  __syncthreads();
+  float alpha[MM];
+  float top = -__builtin_inff();
+#pragma unroll
+  for (int m = 0; m < MM; ++m) {
+    alpha[m] = 0.f;
+    if (m < M) {
+      float v = 0.f;
+      for (int w = 0; w < nw; ++w) v += red[m][w];
+      alpha[m] = v * inv_sqrt_d;
+      top = fmaxf(top, alpha[m]);
+    }
+  }
+  float sum = 0.f;
+#pragma unroll
+  for (int m = 0; m < MM; ++m) {
+    if (m < M) {
+      alpha[m] = expf(alpha[m] - top);
+      sum += alpha[m];
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < MM; ++m) alpha[m] = alpha[m] / sum;
+
+  char* h = hidden + t * h_bytes;
+  auto mix = [&](int c, auto&& row_chunk) {   // row_chunk(m): chunk c of R^m
+    const u32x4_t hv = ld16(h + (int64_t)c * 16);
+    u32x4_t out;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < MM; ++m) {
+      if (m < M) {
+        const u32x4_t rv = row_chunk(m);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if constexpr (DT == DT_BF16) {
+            acc[2 * e] = fmaf(alpha[m], bf16lo(rv[e]), acc[2 * e]);
+            acc[2 * e + 1] = fmaf(alpha[m], bf16hi(rv[e]), acc[2 * e + 1]);
+          } else {
+            acc[e] = fmaf(alpha[m], as_f32(rv[e]), acc[e]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if constexpr (DT == DT_BF16)
+        out[e] = pack_bf16x2(bf16lo(hv[e]) + acc[2 * e], bf16hi(hv[e]) + acc[2 * e + 1]);
+      else
+        out[e] = as_u32(as_f32(hv[e]) + acc[e]);
+    }
+    st16(h + (int64_t)c * 16, out);
+  };
+  if constexpr (C > 0) {
+#pragma unroll
+    for (int x = 0; x < CC; ++x) {
+      const int c = tid + x * (int)blockDim.x;
+      if (c < chunks) mix(c, [&](int m) { return r[m][x]; });
+    }
+  } else {
+    for (int c = tid; c < chunks; c += blockDim.x)
+      mix(c, [&](int m) {
+        int64_t vrow[K];
+        float wt[K];
+        return picks(m, vrow, wt) ? weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c)
+                                  : u32x4_t{0, 0, 0, 0};
+      });
+  }
+}
+
+hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const int32_t* kept,
+                         const int32_t* scene, const int32_t* prim, const float* w,
+                         const void* values, int Sm, int P, int d_v, int k, const void* q,
+                         int d_h, void* hidden, hipStream_t st, const int32_t* count) {
+  const int64_t es = dt == DT_BF16 ? 2 : 4, vb = (int64_t)d_v * es;
+  const int ch = (int)(vb / 16);
+  const int bs = ch >= MS_THREADS ? MS_THREADS : (ch + 63) / 64 * 64;
+  const float inv_sqrt_d = 1.0f / sqrtf((float)d_v);
+#define LOOKME_MS(DT_, K_, MM_, C_)                                                            \
+  hipLaunchKernelGGL((ms_mix_kernel<DT_, K_, MM_, C_>), dim3((unsigned)n_keep), dim3(bs), 0,   \
+                     st, n, kept, scene, prim, w, static_cast<const char*>(values), Sm, P, k,  \
+                     scales, vb, static_cast<const char*>(q), static_cast<char*>(hidden),      \
+                     d_h * es, inv_sqrt_d, count)
+#define LOOKME_MS_C(DT_, K_, MM_)                                  \
+  do {                                                             \
+    if (ch <= MS_THREADS) LOOKME_MS(DT_, K_, MM_, 1);              \
+    else if (ch <= 2 * MS_THREADS) LOOKME_MS(DT_, K_, MM_, 2);     \
+    else LOOKME_MS(DT_, K_, MM_, 0);                               \
+  } while (0)
+#define LOOKME_MS_K(DT_, MM_)                \
+  do {                                       \
+    if (k <= 8) LOOKME_MS_C(DT_, 8, MM_);    \
+    else if (k <= 16) LOOKME_MS_C(DT_, 16, MM_); \
+    else LOOKME_MS_C(DT_, 32, MM_);          \
+  } while (0)
+  if (dt == DT_BF16) {
+    if (scales <= 4) LOOKME_MS_K(DT_BF16, 4);
+    else LOOKME_MS_K(DT_BF16, MS_MAX_SCALES);
+  } else {
+    if (scales <= 4) LOOKME_MS_K(DT_F32, 4);
+    else LOOKME_MS_K(DT_F32, MS_MAX_SCALES);
+  }
+#undef LOOKME_MS_K
+#undef LOOKME_MS_C
+#undef LOOKME_MS
+  return hipGetLastError();
+}
+
 template <int DT, bool TO_R = false>
 static void launch_inject_k(int kk, dim3 grid, hipStream_t st, int64_t n, int64_t n_keep,
                             const int32_t* kept, const int32_t* scene, const int32_t* prim,

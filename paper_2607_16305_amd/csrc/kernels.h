@@ -187,15 +187,19 @@ hipError_t launch_propagate(int dt, const void* w_p_t, int steps, int64_t n_keep
 
 // ---- multi-scale retrieval with the token-wise router (Eq. 8) -------------
 // Scale m's lookup (scene [M, n] local to partition m of S / M scenes, prim
-// and w [M, n, k]) gives R^m of every kept token, gathered and rounded into
-// r [M, n_keep, d_v]; q = round(H[kept] W_he) into q [n_keep, d_v] (w_he_t
-// [d_v, d_h], output-row-major); then H[t, :d_v] = round(H + sum_m alpha_m
-// R^m) with alpha = softmax_m(q . R^m / sqrt(d_v)).
+// and w [M, n, k]) gives R^m of every kept token; q = round(H[kept] W_he) into
+// q [n_keep, d_v] (w_he_t [d_v, d_h], output-row-major); then H[t, :d_v] =
+// round(H + sum_m alpha_m R^m) with alpha = softmax_m(q . R^m / sqrt(d_v))
+// (launch_ms_mix).
 constexpr int MS_MAX_SCALES = 8;
+hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const int32_t* kept,
+                         const int32_t* scene, const int32_t* prim, const float* w,
+                         const void* values, int Sm, int P, int d_v, int k, const void* q,
+                         int d_h, void* hidden, hipStream_t st, const int32_t* count);
 hipError_t launch_multiscale(int dt, int scales, int64_t n, int64_t n_keep, const int32_t* kept,
                              const int32_t* scene, const int32_t* prim, const float* w,
                              const void* values, int S, int P, int d_v, int k,
-                             const void* w_he_t, int d_h, void* hidden, void* r, void* q,
+                             const void* w_he_t, int d_h, void* hidden, void* q,
                              hipStream_t st, const int32_t* count = nullptr);
 
 // ---- Level-2 scoring of bucketed rows, fused top-k + softmax --------------
