@@ -23,6 +23,18 @@ __device__ __forceinline__ void load_lds16_nt(const void* src, char* lds_dst) {
   __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)lds_dst, 16, 0, 2);
 }
 
+// One direct global-to-LDS load of 16 bytes per lane from a uniform base plus a
+// 32-bit lane offset plus a uniform offset: a buffer load, whose address
+// needs no vector register beside the lane offset and no vector instruction
+// (the caller keeps every address inside the operand).
+__device__ __forceinline__ void load_lds16_at(const void* base, uint32_t lane_off, int uniform_off,
+                                              char* lds_dst) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<void*>(base), 0, 0xffffffff, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)lds_dst, 16, (int)lane_off, uniform_off,
+                                           0, 0);
+}
+
 // chunk c of row r of a block sits in slot c ^ blk_swz(r): rows that share a
 // bank window get distinct slots for one chunk index.  For 128-byte rows,
 // r & 7 lets a fragment read (16 rows, one chunk index) run at ~210 bytes

@@ -14,7 +14,12 @@
 //
 // Two stage buffers thus carry almost two stages of loads in flight (a part
 // has seven phases to arrive), and no product waits for an LDS read of its
-// own phase.  The weights' rows are MFMA operand A and the tokens' rows
+// own phase.  The loads are buffer loads (load_lds16_at): with 64-bit
+// addresses each took vector instructions and two registers beside the 240
+// that accumulators and fragments fill (23040 x 2048 x 2048 193.7 -> 185.5
+// us, 1042 TFLOP/s; 32768 x 512 x 4096 113 us, 1216).  What bounds it now:
+// without the loads 98 us of those 113, without the products 76, so the
+// stage stream out of L2 and the LDS it shares with the fragment reads.  The weights' rows are MFMA operand A and the tokens' rows
 // operand B, with the weight rows of the NJ tiles of a wave dealt so that a
 // lane ends with 4 NJ neighbouring columns of one output row: the epilogues
 // read and write 16 bytes a lane.
@@ -47,16 +52,15 @@ __device__ __forceinline__ int pg_swz(int r) {
 
 // The accumulators of A B^T for the tile: acc[qi][qj][i][j] element r is
 // row 16 MI wr + 16 i + n16 of A half qi and column 16 NJ wc + W g + 4 j + r
-// of B half qj (wave (wr, wc), lane (g, n16)).  pa[h][q], pb[h][q]: the
-// lane's source of load q of a part of half h (row base + chunk); lds: 2 BUF
-// bytes, all waves of the workgroup take part.
+// of B half qj (wave (wr, wc), lane (g, n16)).  lds: 2 BUF bytes, all waves
+// of the workgroup take part.  The loads come from the caller: ld.a(h, stage,
+// dst) issues this wave's PA loads of A half h of a stage to dst (1 KiB
+// each), ld.b the PB loads of a B half, and ld.next() ends a stage's loads.
 template <int DT, int MI, int NJ>
 struct PgLoop {
   using S = PgShape<MI, NJ>;
   char* lds;
   int lane, wv, n16, g, wr, wc;
-  const char* pa[2][S::PA];
-  const char* pb[2][S::PB];
 
   __device__ __forceinline__ PgLoop(char* l, int tid) : lds(l) {
     lane = tid & 63;
@@ -72,17 +76,11 @@ struct PgLoop {
   __device__ __forceinline__ int a_chunk(int q) const { return (lane & 7) ^ pg_swz<1>(a_row(q)); }
   __device__ __forceinline__ int b_chunk(int q) const { return (lane & 7) ^ pg_swz<NJ>(b_row(q)); }
 
-  __device__ __forceinline__ void load_a(int h, int stage, int last) const {
-    const int64_t k = (int64_t)(stage < last ? stage : last) * 128;   // past the end: reread
-    char* dst = lds + (stage & 1) * S::BUF + h * S::A_PART + wv * S::PA * 1024;
-#pragma unroll
-    for (int q = 0; q < S::PA; ++q) load_lds16(pa[h][q] + k, dst + q * 1024);
+  __device__ __forceinline__ char* a_dst(int h, int stage) const {
+    return lds + (stage & 1) * S::BUF + h * S::A_PART + wv * S::PA * 1024;
   }
-  __device__ __forceinline__ void load_b(int h, int stage, int last) const {
-    const int64_t k = (int64_t)(stage < last ? stage : last) * 128;
-    char* dst = lds + (stage & 1) * S::BUF + 2 * S::A_PART + h * S::B_PART + wv * S::PB * 1024;
-#pragma unroll
-    for (int q = 0; q < S::PB; ++q) load_lds16(pb[h][q] + k, dst + q * 1024);
+  __device__ __forceinline__ char* b_dst(int h, int stage) const {
+    return lds + (stage & 1) * S::BUF + 2 * S::A_PART + h * S::B_PART + wv * S::PB * 1024;
   }
   __device__ __forceinline__ void read_a(int h, int stage, u32x4_t (&f)[2][MI]) const {
     const char* p = lds + (stage & 1) * S::BUF + h * S::A_PART + (wr * 16 * MI + n16) * 128;
@@ -108,18 +106,12 @@ struct PgLoop {
                                              const u32x4_t (&fb)[2][NJ],
                                              f32x4_t (&acc)[MI][NJ]) {
     __builtin_amdgcn_sched_barrier(0);
-#ifdef PG_PRIO
-    __builtin_amdgcn_s_setprio(1);
-#endif
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = mfma_chunk<DT>(fb[ks][j], fa[ks][i], acc[i][j]);
-#ifdef PG_PRIO
-    __builtin_amdgcn_s_setprio(0);
-#endif
   }
   // ends a phase: this wave's LDS reads have returned and all but the V
   // youngest of its loads have landed; then the barrier (a plain s_barrier:
@@ -136,32 +128,43 @@ struct PgLoop {
 
   // one stage; fb0 holds B0(s), fb1 receives B1(s) and then B0(s + 1)
   // (before phase k the part it reads is the oldest of the seven loaded
-  // last: the six younger ones may be in flight)
-  __device__ __forceinline__ void stage(int s, int last, f32x4_t (&acc)[2][2][MI][NJ],
+  // last: the six younger ones may be in flight).  done(q): quadrant q
+  // (2 qi + qj) of the stage has been multiplied; called in the next phase,
+  // beside its products, and for the last one at the end.
+  template <class Ld, class Done>
+  __device__ __forceinline__ void stage(int s, Ld& ld, f32x4_t (&acc)[2][2][MI][NJ],
                                         u32x4_t (&fa0)[2][MI], u32x4_t (&fa1)[2][MI],
-                                        u32x4_t (&fb0)[2][NJ], u32x4_t (&fb1)[2][NJ]) const {
+                                        u32x4_t (&fb0)[2][NJ], u32x4_t (&fb1)[2][NJ],
+                                        Done&& done) const {
     constexpr int PA = S::PA, PB = S::PB;
     sync<4 * PA + 2 * PB>();
     read_b(1, s, fb1);
-    load_b(0, s + 2, last);
+    ld.b(0, s + 2, b_dst(0, s + 2));
     mma(fa0, fb0, acc[0][0]);
     sync<3 * PA + 3 * PB>();
     read_a(1, s, fa1);
-    load_b(1, s + 2, last);
+    ld.b(1, s + 2, b_dst(1, s + 2));
     mma(fa0, fb1, acc[0][1]);
+    done(0);
     sync<2 * PA + 4 * PB>();
     read_a(0, s + 1, fa0);
-    load_a(1, s + 2, last);
+    ld.a(1, s + 2, a_dst(1, s + 2));
     mma(fa1, fb1, acc[1][1]);
+    done(1);
     sync<3 * PA + 3 * PB>();
     read_b(0, s + 1, fb1);
-    load_a(0, s + 3, last);
+    ld.next();
+    ld.a(0, s + 3, a_dst(0, s + 3));
     mma(fa1, fb0, acc[1][0]);
+    done(3);
+    done(2);
   }
 
-  __device__ __forceinline__ void run(int nst, f32x4_t (&acc)[2][2][MI][NJ]) const {
+  // done(s, q): see stage
+  template <class Ld, class Done>
+  __device__ __forceinline__ void run(int nst, Ld& ld, f32x4_t (&acc)[2][2][MI][NJ],
+                                      Done&& done) const {
     constexpr int PA = S::PA, PB = S::PB;
-    const int last = nst - 1;
 #pragma unroll
     for (int qi = 0; qi < 2; ++qi)
 #pragma unroll
@@ -171,27 +174,50 @@ struct PgLoop {
 #pragma unroll
           for (int j = 0; j < NJ; ++j) acc[qi][qj][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     u32x4_t fa0[2][MI], fa1[2][MI], fbx[2][NJ], fby[2][NJ];
-    load_a(0, 0, last);
-    load_b(0, 0, last);
-    load_b(1, 0, last);
-    load_a(1, 0, last);
-    load_a(0, 1, last);
-    load_b(0, 1, last);
-    load_b(1, 1, last);
-    load_a(1, 1, last);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      ld.a(0, s, a_dst(0, s));
+      ld.b(0, s, b_dst(0, s));
+      ld.b(1, s, b_dst(1, s));
+      ld.a(1, s, a_dst(1, s));
+      ld.next();
+    }
     sync<3 * PA + 3 * PB>();   // A0(0) and B0(0) have landed
     read_a(0, 0, fa0);
     read_b(0, 0, fbx);
     sync<3 * PA + 3 * PB>();   // and every wave has read A0(0)
-    load_a(0, 2, last);
+    ld.a(0, 2, a_dst(0, 2));
     int s = 0;
     for (; s + 1 < nst; s += 2) {
-      stage(s, last, acc, fa0, fa1, fbx, fby);
-      stage(s + 1, last, acc, fa0, fa1, fby, fbx);
+      stage(s, ld, acc, fa0, fa1, fbx, fby, [&](int q) { done(s, q); });
+      stage(s + 1, ld, acc, fa0, fa1, fby, fbx, [&](int q) { done(s + 1, q); });
     }
-    if (s < nst) stage(s, last, acc, fa0, fa1, fbx, fby);
+    if (s < nst) stage(s, ld, acc, fa0, fa1, fbx, fby, [&](int q) { done(s, q); });
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // no load into LDS outlives the wave
   }
+};
+
+// The loads of one tile of A B^T: uniform bases (of the tile's A rows, of
+// each B half) and 32-bit lane offsets of load q of a part of half h (row +
+// chunk).  Past the last stage it is read again, so that the waits keep their
+// counts.
+template <class S>
+struct PgLoads {
+  const char* a_base;
+  const char* b_base[2];
+  uint32_t oa[2][S::PA], ob[2][S::PB];
+  int last;
+  __device__ __forceinline__ void a(int h, int stage, char* dst) const {
+    const int k = (stage < last ? stage : last) * 128;
+#pragma unroll
+    for (int q = 0; q < S::PA; ++q) load_lds16_at(a_base, oa[h][q], k, dst + q * 1024);
+  }
+  __device__ __forceinline__ void b(int h, int stage, char* dst) const {
+    const int k = (stage < last ? stage : last) * 128;
+#pragma unroll
+    for (int q = 0; q < S::PB; ++q) load_lds16_at(b_base[h], ob[h][q], k, dst + q * 1024);
+  }
+  __device__ __forceinline__ void next() const {}
 };
 
 // W neighbouring elements of a row as float32, and back with one rounding.

@@ -425,8 +425,12 @@ __device__ __forceinline__ void phase_tile(const TileGemmParams& a, char* lds, i
   using S = PgShape<MI, NJ>;
   constexpr int ES = DT == DT_BF16 ? 2 : 4, W = S::W;
   PgLoop<DT, MI, NJ> L(lds, threadIdx.x);
+  PgLoads<S> ld;
+  ld.last = (int)(a.k_bytes / 128) - 1;
   {
-    const char* A0 = a.a0 + z * a.a_batch;
+    // gathered rows (a_sel) count from the operand's first row, others from
+    // the tile's
+    ld.a_base = a.a0 + z * a.a_batch + (a.a_sel != nullptr ? 0 : m0 * a.a_bytes);
     const int64_t bld = a.b_ld != 0 ? a.b_ld : a.k_bytes;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -437,20 +441,24 @@ __device__ __forceinline__ void phase_tile(const TileGemmParams& a, char* lds, i
         if (a.a_sel != nullptr) {
           const int s = a.a_sel[r];
           r = s < 0 ? 0 : (s >= a.sel_rows ? a.sel_rows - 1 : s);
+        } else {
+          r -= m0;
         }
-        L.pa[h][q] = A0 + r * a.a_bytes + L.a_chunk(q) * 16;
+        ld.oa[h][q] = (uint32_t)(r * a.a_bytes) + L.a_chunk(q) * 16;
       }
-      const char* B = EPI == EPI_SWIGLU && h == 1 ? a.b2 : a.b;
+      const int nh = n0 + (EPI == EPI_SWIGLU ? 0 : h * S::HN);   // first B row of the half
+      const int first = nh < a.cols ? nh : a.cols - 1;
+      ld.b_base[h] = (EPI == EPI_SWIGLU && h == 1 ? a.b2 : a.b) + z * a.b_batch + first * bld;
 #pragma unroll
       for (int q = 0; q < S::PB; ++q) {
-        int r = n0 + (EPI == EPI_SWIGLU ? 0 : h * S::HN) + L.b_row(q);
+        int r = nh + L.b_row(q);
         r = r < a.cols ? r : a.cols - 1;
-        L.pb[h][q] = B + z * a.b_batch + r * bld + L.b_chunk(q) * 16;
+        ld.ob[h][q] = (uint32_t)((r - first) * bld) + L.b_chunk(q) * 16;
       }
     }
   }
   f32x4_t acc[2][2][MI][NJ];
-  L.run((int)(a.k_bytes / 128), acc);
+  L.run(ld.last + 1, ld, acc, [](int, int) {});
 
   constexpr int QJ = EPI == EPI_SWIGLU ? 1 : 2;
   int col[QJ];
@@ -557,13 +565,16 @@ __global__ __launch_bounds__(512, 2) void phase_gemm_kernel(TileGemmParams a) {
   int tile = whole ? xcd_remap(blockIdx.x, pl.whole)
                    : xcd_remap((int)blockIdx.x - first_cut, 4 * pl.cut);
   if (tile < 0) return;
+  // (quotients come out of vector instructions: said to be uniform, so that
+  // the operands' bases stay in scalar registers)
+  tile = __builtin_amdgcn_readfirstlane(tile);
   const int quarter = tile & 3;
   if (!whole) tile = pl.whole + (tile >> 2);
   int z = 0;
   int64_t rows = live(0);
   if (a.count == nullptr || a.count_step == 0) {
     const int per = tiles_of(rows);
-    z = tile / per;
+    z = __builtin_amdgcn_readfirstlane(tile / per);
     tile -= z * per;
   } else {
     for (int per = tiles_of(rows); tile >= per; per = tiles_of(rows)) {
@@ -573,8 +584,9 @@ __global__ __launch_bounds__(512, 2) void phase_gemm_kernel(TileGemmParams a) {
   }
   int64_t m0;
   int n0;
-  m0 = (int64_t)(tile / tn) * S::BM;
-  n0 = (tile % tn) * TCOLS;
+  const int tm = __builtin_amdgcn_readfirstlane(tile / tn);
+  m0 = (int64_t)tm * S::BM;
+  n0 = (tile - tm * tn) * TCOLS;
   if (whole) {
     phase_tile<DT, EPI, 4, 2>(a, lds, z, rows, m0, n0);
   } else {
@@ -625,7 +637,10 @@ hipError_t launch_tile_gemm(int dt, TileGemmParams p, int batches, hipStream_t s
   // by the matrix cores on either, and 64 x 64 tiles fill the last round
   // better: from 512 tiles on (16384 x 2048 x 1024 607 -> 561 us; 8192 x 1024
   // x 1024, 128 tiles, 166 and 172).
-  if (p.cols % 8 == 0 && phase_tiles<EPI>(p, batches) >= (dt == DT_BF16 ? 48 : 512))
+  // Its lane offsets are 32-bit: rows below 8 MiB, gathered rows inside 4 GiB.
+  const bool near = p.a_bytes < (8 << 20) && p.k_bytes < (8 << 20) && p.b_ld < (8 << 20) &&
+                    (p.a_sel == nullptr || p.sel_rows * p.a_bytes < ((int64_t)1 << 32));
+  if (p.cols % 8 == 0 && near && phase_tiles<EPI>(p, batches) >= (dt == DT_BF16 ? 48 : 512))
     return launch_phase<EPI>(dt, p, batches, st);
   const unsigned gx = (unsigned)((p.tiles + 7) / 8 * 8);
   const dim3 grid(gx, (unsigned)batches);
