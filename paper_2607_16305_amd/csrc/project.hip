@@ -222,9 +222,15 @@ hipError_t launch_project(int dt, const void* x, const void* wt, void* q, int64_
   const int es = dt == DT_BF16 ? 2 : 4;
   const int N = layers * d_e;
   const int64_t kb = (int64_t)d_in * es;
+  // The 32 x 64 tiles below split K over four wave groups, one workgroup a CU:
+  // right while every tile has a CU of its own (1024 x 512 x 2048, 256 tiles:
+  // 10.9 us against 12.1 on 64 x 64 tiles), slow after (2000 x 512 x 2048
+  // 20.1 and 12.8 us, 4000 x 512 x 2048 40.1 and 16.6, 2000 x 2048 x 512 49.3
+  // and 11.1).  float32 keeps them until the chip is full of 128 x 128 tiles:
+  // its sums are stored as they are, and four partial sums err less than one.
   const int64_t tiles128 = ((n + 127) / 128) * ((N + 127) / 128);
-  if (kb % TG_KB == 0 && tiles128 >= 256) {
-    // enough tiles to fill the chip: the phased kernel or 64 x 64 tiles
+  const int64_t tiles_k4 = ((n + 31) / 32) * ((N + 63) / 64);
+  if (kb % TG_KB == 0 && (dt == DT_BF16 ? tiles_k4 > 256 : tiles128 >= 256)) {
     TileGemmParams p{};
     p.a0 = static_cast<const char*>(x);
     p.b = static_cast<const char*>(wt);
