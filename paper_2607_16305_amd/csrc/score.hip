@@ -867,45 +867,48 @@ static int route_unit_rows(int64_t rows, int shared_rows) {
 
 static int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-// Key ranges per row block of the tile kernel (at least `least`, so that a
-// unit's bias table fits its LDS).  The kernel runs one workgroup a CU (its
-// LDS): when the row blocks alone fill whole rounds of the 256 CUs to 90%,
-// no split (each unit walks every key tile, no partial lists to merge;
-// Zipf batch 176 -> 164 us against two splits); else about 512 workgroups
-// (measured better than rounds filled with one-tile units, whose pipeline
-// start and merge cost more than a partial round's idle CUs: multi-scale
-// batch 51 us with 2 splits, 55 with 4).
-static int route_splits(int64_t blocks, int tiles, int least) {
-  const double fill = (double)blocks / (double)(cdiv(blocks, 256) * 256);
-  if (least <= 1 && fill >= 0.9) return 1;
-  int sp = blocks < 512 ? cdiv(512, blocks) : 1;
-  sp = sp < tiles ? sp : tiles;
-  return sp > least ? sp : least;
+// Rows per block and key ranges per row block of the tile kernel, which runs
+// one workgroup a CU: the choice with the least time by a fit to measured
+// times (bf16, 1 KiB keys): a round of 256 units takes 1.69 us a K stage of
+// 256 x 256 and 6 us for its first loads and its end (128 x 256: 1.05 and
+// 4), and 3 us more where the ranges of a block are merged.  Measured, best
+// plans of 256- and of 128-row blocks: 32768 rows x 4096 keys 149.8 (two
+// ranges) and 150.3 us, 92160 x 1024 111.6 and 111.9, 46080 x 4096 199.8
+// (four ranges) and 219, 60000 x 300 36.1 and 40.7, 20000 x 500 21.9 and
+// 20.5, 8192 x 1024 22.2 and 17.6 (four ranges), 4096 x 256 18.3 and 11.4.
+// The kernel before (three-stage ring, 128-row blocks) at its best plans:
+// 159.6, 116.6, 212, 45.3, 21.1, 20.2, 13.7; the scoring kernel's shared mode
+// 169 at 92160 x 1024.  A unit's bias table holds ROUTE_DTL_MAX_TPS tiles
+// (and leaves no LDS for 256-row blocks), and split blocks have an arrival
+// counter each.
+static RoutePlan route_tile_plan(int64_t rows, int S, int64_t row_bytes, bool bias) {
+  RoutePlan best{ROUTE_DTL, 0, 0, 0, 0};
+  const int tiles = cdiv(S, ROUTE_DTL_KEYS);
+  double least = 0.;
+  for (int br = bias ? 128 : 256; br >= 128; br /= 2) {
+    const int64_t blocks = (rows + br - 1) / br;
+    const double stage = br == 256 ? 1.69 : 1.05, unit = br == 256 ? 6. : 4.;
+    for (int sp = 1; sp < 2 * tiles; sp *= 2) {
+      const int tps = cdiv(tiles, sp), n = cdiv(tiles, tps);
+      if (tps > ROUTE_DTL_MAX_TPS || (n > 1 && blocks > ROUTE_COUNTERS)) continue;
+      const double t = (double)cdiv(blocks * n, 256) *
+                       (tps * (double)(row_bytes / 128) * stage + unit + (n > 1 ? 3. : 0.));
+      if (best.splits == 0 || t < least) {
+        least = t;
+        best = RoutePlan{ROUTE_DTL, n, tps, n > 1 ? blocks * n * br : 0, br};
+      }
+    }
+  }
+  return best;
 }
 
-RoutePlan route_plan(int64_t rows, int S, int64_t row_bytes, bool cos) {
-  RoutePlan p{ROUTE_SHARED, 1, S, 0};
+RoutePlan route_plan(int64_t rows, int S, int64_t row_bytes, bool cos, bool bias) {
+  RoutePlan p{ROUTE_SHARED, 1, S, 0, 0};
   if (rows <= 0 || S <= 0) return p;
-  const int64_t blocks = (rows + ROUTE_DTL_ROWS - 1) / ROUTE_DTL_ROWS;
   // the tile kernel scores dot products only
-  if (!cos && rows >= ROUTE_DTL_MIN_ROWS && blocks < ROUTE_DTL_MAX_BLOCKS &&
-      row_bytes % 128 == 0) {
-    // enough 128-row blocks for the matrix-core kernel but too few to fill
-    // the chip with the shared-mode units; split the key tiles until about
-    // 512 workgroups run (and at most ROUTE_DTL_MAX_TPS tiles stay with one
-    // workgroup, whose bias table lives in LDS)
-    const int tiles = cdiv(S, ROUTE_DTL_KEYS);
-    const int least = cdiv(tiles, ROUTE_DTL_MAX_TPS);
-    int sp = route_splits(blocks, tiles, least);
-    const int tps = cdiv(tiles, sp);
-    sp = cdiv(tiles, tps);
-    if (sp == 1 || blocks <= ROUTE_COUNTERS) {
-      p.mode = ROUTE_DTL;
-      p.splits = sp;
-      p.per_split = tps;
-      p.part_entries = sp > 1 ? blocks * sp * ROUTE_DTL_ROWS : 0;
-      return p;
-    }
+  if (!cos && rows >= ROUTE_DTL_MIN_ROWS && row_bytes % 128 == 0) {
+    const RoutePlan t = route_tile_plan(rows, S, row_bytes, bias);
+    if (t.splits > 0) return t;
   }
   if (route_unit_rows(rows, shared_unit_rows(row_bytes, 0)) == UNIT_STREAM_ROWS) {
     // small batch: split the keys of every 16-row tile (at least 64 keys a
@@ -942,7 +945,7 @@ hipError_t launch_route(int dt, const void* q, const void* scene_keys, const flo
   p.route_rows = route_unit_rows(rows, shared_unit_rows(p.row_bytes, 0));
   p.out_idx = scene;
   p.cos = cos ? 1 : 0;
-  const RoutePlan plan = route_plan(rows, S, p.row_bytes, cos);
+  const RoutePlan plan = route_plan(rows, S, p.row_bytes, cos, bias != nullptr);
   if (plan.mode == ROUTE_DTL)
     return launch_route_dtl(dt, q, scene_keys, bias, scene, rows, d_e, S, plan, part, count, st);
   p.route_rows = plan.mode == ROUTE_STREAM ? UNIT_STREAM_ROWS : p.route_rows;
