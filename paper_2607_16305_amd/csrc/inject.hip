@@ -155,15 +155,23 @@ __global__ __launch_bounds__(INJ_THREADS) void inject_kernel(
 // The multi-scale mix (Eq. 8) of one kept row j: the M scales' rows R^m (k
 // table rows each, weighted and rounded as the gather form writes them),
 // their products with the token's query, the softmax over the scales and the
-// weighted sum added into the token's hidden row.  The R^m stay in registers
-// between their two uses (C 16-byte chunks of each a thread): written to
-// memory by a gather launch and read back twice they were 210 MB on 11520
-// rows of two scales, and the two launches took 91 + 38.5 us (the whole gated
-// injection 237 -> 210 us).  Rows of more than 2 x 256
-// chunks (C = 0) gather twice instead.  Bound by the gather's traffic behind
-// the caches, like the injection above, so one workgroup a row and every
-// chunk load of a thread in flight together.
-constexpr int MS_THREADS = 256;
+// weighted sum added into the token's hidden row.  The R^m stay in LDS
+// between their two uses: written to memory by a gather launch and read back
+// twice they were 210 MB on 11520 rows of two scales, and the two launches
+// took 91 + 38.5 us (the whole gated injection 237 -> 207 us).  Bound by the
+// gather's traffic behind the caches, like the injection above; on few rows
+// by its chain of dependent loads (kept row, scene, picks, values), so below
+// MS_MANY_ROWS rows the scales of a row go to thread groups of their own,
+// side by side (500 float32 rows of four scales, the whole injection 44.7 ->
+// 35.5 us against one after another); with many rows the chip is full of them
+// and narrow workgroups run better (3000 rows of four scales 104 -> 86 us,
+// 23040 of two 235 -> 207).  Rows whose R^m do not fit the LDS (LDS = false)
+// gather twice instead.
+constexpr int MS_GROUP = 256;              // threads of a scale at most
+constexpr int64_t MS_MANY_ROWS = 2048;
+constexpr int MS_LDS_BYTES = 60 * 1024;    // R^m of a row
+// threads of a row at most (k > 16 holds more loads in registers)
+constexpr int ms_threads(int k) { return k > 16 ? 512 : 1024; }
 
 template <int DT, int K>
 __device__ __forceinline__ u32x4_t weighted_chunk(const char* __restrict__ values,
@@ -212,22 +220,25 @@ __device__ __forceinline__ float chunk_dot(u32x4_t a, u32x4_t b, float acc) {
   return acc;
 }
 
-// MM: scales compiled for (M <= MM).  A row whose token id is out of range is
-// left alone and counted once a scale; a scale whose scene or a primitive is
-// out of range has R^m = 0 and is counted.
-template <int DT, int K, int MM, int C>
-__global__ __launch_bounds__(MS_THREADS) void ms_mix_kernel(
+// groups x gs threads: group y takes scales y, y + groups, ...  A row whose
+// token id is out of range is left alone and counted once a scale; a scale
+// whose scene or a primitive is out of range has R^m = 0 and is counted.
+template <int DT, int K, bool LDS>
+__global__ __launch_bounds__(ms_threads(K)) void ms_mix_kernel(
     int64_t n, const int32_t* __restrict__ kept, const int32_t* __restrict__ scene_all,
     const int32_t* __restrict__ prim_all, const float* __restrict__ w_all,
     const char* __restrict__ values, int Sm, int P, int k, int M, int64_t v_bytes,
     const char* __restrict__ q, char* __restrict__ hidden, int64_t h_bytes, float inv_sqrt_d,
-    const int32_t* __restrict__ count) {
-  constexpr int CC = C > 0 ? C : 1;
-  __shared__ float red[MM][MS_THREADS / WAVE];
+    const int32_t* __restrict__ count, int gs) {
+  __shared__ float red[MS_MAX_SCALES][MS_GROUP / WAVE];
+  extern __shared__ __attribute__((aligned(16))) char rows_lds[];   // [M, v_bytes] (LDS)
   const int64_t j = blockIdx.x;
   if (count != nullptr && j >= *count) return;   // past a counted list's end
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int nw = (int)(blockDim.x / WAVE);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int groups = (int)blockDim.x / gs, nw = gs / WAVE;
+  // the group (whole waves), and the thread's place in it
+  const int y = __builtin_amdgcn_readfirstlane(tid / gs);
+  const int gt = tid - y * gs, wv = gt >> 6;
   const int64_t t = kept[j];
   if (t < 0 || t >= n) {
     if (tid == 0) atomicAdd(&g_index_errors, (unsigned long long)M);
@@ -236,8 +247,8 @@ __global__ __launch_bounds__(MS_THREADS) void ms_mix_kernel(
   const int chunks = (int)(v_bytes / 16);
   const char* qrow = q + j * v_bytes;
 
-  // scale m's table rows and weights (uniform over the workgroup); false:
-  // an index out of range
+  // scale m's table rows and weights (uniform over the group); false: an
+  // index out of range
   auto picks = [&](int m, int64_t (&vrow)[K], float (&wt)[K]) {
     const int64_t row = (int64_t)m * n + t;
     const int s = scene_all[row];
@@ -258,48 +269,28 @@ __global__ __launch_bounds__(MS_THREADS) void ms_mix_kernel(
     return ok;
   };
 
-  u32x4_t r[MM][CC];
-  float dot[MM];
-#pragma unroll
-  for (int m = 0; m < MM; ++m) {
-    dot[m] = 0.f;
-    if (m < M) {
-      int64_t vrow[K];
-      float wt[K];
-      const bool ok = picks(m, vrow, wt);
-      if (!ok && tid == 0) atomicAdd(&g_index_errors, 1ull);
-      if constexpr (C > 0) {
-#pragma unroll
-        for (int x = 0; x < CC; ++x) {
-          const int c = tid + x * (int)blockDim.x;
-          r[m][x] = u32x4_t{0, 0, 0, 0};
-          if (ok && c < chunks) {
-            r[m][x] = weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c);
-            dot[m] = chunk_dot<DT>(ld16(qrow + (int64_t)c * 16), r[m][x], dot[m]);
-          }
-        }
-      } else {
-        if (ok)
-          for (int c = tid; c < chunks; c += blockDim.x)
-            dot[m] = chunk_dot<DT>(ld16(qrow + (int64_t)c * 16),
-                                   weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c), dot[m]);
+  for (int m = y; m < M; m += groups) {
+    int64_t vrow[K];
+    float wt[K], dot = 0.f;
+    const bool ok = picks(m, vrow, wt);
+    for (int c = gt; c < chunks; c += gs) {
+      u32x4_t r = {0, 0, 0, 0};
+      if (ok) {
+        r = weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c);
+        dot = chunk_dot<DT>(ld16(qrow + (int64_t)c * 16), r, dot);
       }
+      if constexpr (LDS) *reinterpret_cast<u32x4_t*>(rows_lds + m * v_bytes + c * 16) = r;
     }
-  }
 #pragma unroll
-  for (int m = 0; m < MM; ++m) {
-    if (m < M) {
-      float v = dot[m];
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-      if (lane == 0) red[m][wv] = v;
-    }
+    for (int d = 32; d >= 1; d >>= 1) dot += __shfl_xor(dot, d, 64);
+    if (lane == 0) red[m][wv] = dot;
+    if (!ok && gt == 0) atomicAdd(&g_index_errors, 1ull);
   }
   __syncthreads();
-  float alpha[MM];
+  float alpha[MS_MAX_SCALES];
   float top = -__builtin_inff();
 #pragma unroll
-  for (int m = 0; m < MM; ++m) {
+  for (int m = 0; m < MS_MAX_SCALES; ++m) {
     alpha[m] = 0.f;
     if (m < M) {
       float v = 0.f;
@@ -310,24 +301,32 @@ __global__ __launch_bounds__(MS_THREADS) void ms_mix_kernel(
   }
   float sum = 0.f;
 #pragma unroll
-  for (int m = 0; m < MM; ++m) {
+  for (int m = 0; m < MS_MAX_SCALES; ++m) {
     if (m < M) {
       alpha[m] = expf(alpha[m] - top);
       sum += alpha[m];
     }
   }
 #pragma unroll
-  for (int m = 0; m < MM; ++m) alpha[m] = alpha[m] / sum;
+  for (int m = 0; m < MS_MAX_SCALES; ++m) alpha[m] = alpha[m] / sum;
 
   char* h = hidden + t * h_bytes;
-  auto mix = [&](int c, auto&& row_chunk) {   // row_chunk(m): chunk c of R^m
+  for (int c = tid; c < chunks; c += blockDim.x) {
     const u32x4_t hv = ld16(h + (int64_t)c * 16);
     u32x4_t out;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int m = 0; m < MM; ++m) {
+    for (int m = 0; m < MS_MAX_SCALES; ++m) {
       if (m < M) {
-        const u32x4_t rv = row_chunk(m);
+        u32x4_t rv;
+        if constexpr (LDS) {
+          rv = *reinterpret_cast<const u32x4_t*>(rows_lds + m * v_bytes + c * 16);
+        } else {
+          int64_t vrow[K];
+          float wt[K];
+          rv = picks(m, vrow, wt) ? weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c)
+                                  : u32x4_t{0, 0, 0, 0};
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           if constexpr (DT == DT_BF16) {
@@ -347,21 +346,6 @@ __global__ __launch_bounds__(MS_THREADS) void ms_mix_kernel(
         out[e] = as_u32(as_f32(hv[e]) + acc[e]);
     }
     st16(h + (int64_t)c * 16, out);
-  };
-  if constexpr (C > 0) {
-#pragma unroll
-    for (int x = 0; x < CC; ++x) {
-      const int c = tid + x * (int)blockDim.x;
-      if (c < chunks) mix(c, [&](int m) { return r[m][x]; });
-    }
-  } else {
-    for (int c = tid; c < chunks; c += blockDim.x)
-      mix(c, [&](int m) {
-        int64_t vrow[K];
-        float wt[K];
-        return picks(m, vrow, wt) ? weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c)
-                                  : u32x4_t{0, 0, 0, 0};
-      });
   }
 }
 
@@ -371,34 +355,31 @@ hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const in
                          int d_h, void* hidden, hipStream_t st, const int32_t* count) {
   const int64_t es = dt == DT_BF16 ? 2 : 4, vb = (int64_t)d_v * es;
   const int ch = (int)(vb / 16);
-  const int bs = ch >= MS_THREADS ? MS_THREADS : (ch + 63) / 64 * 64;
+  const int gs = ch >= MS_GROUP ? MS_GROUP : (ch + 63) / 64 * 64;
+  const int most = n_keep < MS_MANY_ROWS ? ms_threads(k) / gs : 1;
+  const int groups = scales < most ? scales : most;
   const float inv_sqrt_d = 1.0f / sqrtf((float)d_v);
-#define LOOKME_MS(DT_, K_, MM_, C_)                                                            \
-  hipLaunchKernelGGL((ms_mix_kernel<DT_, K_, MM_, C_>), dim3((unsigned)n_keep), dim3(bs), 0,   \
-                     st, n, kept, scene, prim, w, static_cast<const char*>(values), Sm, P, k,  \
-                     scales, vb, static_cast<const char*>(q), static_cast<char*>(hidden),      \
-                     d_h * es, inv_sqrt_d, count)
-#define LOOKME_MS_C(DT_, K_, MM_)                                  \
-  do {                                                             \
-    if (ch <= MS_THREADS) LOOKME_MS(DT_, K_, MM_, 1);              \
-    else if (ch <= 2 * MS_THREADS) LOOKME_MS(DT_, K_, MM_, 2);     \
-    else LOOKME_MS(DT_, K_, MM_, 0);                               \
-  } while (0)
-#define LOOKME_MS_K(DT_, MM_)                \
-  do {                                       \
-    if (k <= 8) LOOKME_MS_C(DT_, 8, MM_);    \
-    else if (k <= 16) LOOKME_MS_C(DT_, 16, MM_); \
-    else LOOKME_MS_C(DT_, 32, MM_);          \
+  const bool lds = scales * vb <= MS_LDS_BYTES;
+#define LOOKME_MS(DT_, K_, L_)                                                                  \
+  hipLaunchKernelGGL((ms_mix_kernel<DT_, K_, L_>), dim3((unsigned)n_keep), dim3(gs * groups),   \
+                     L_ ? (unsigned)(scales * vb) : 0u, st, n, kept, scene, prim, w,            \
+                     static_cast<const char*>(values), Sm, P, k, scales, vb,                    \
+                     static_cast<const char*>(q), static_cast<char*>(hidden), d_h * es,         \
+                     inv_sqrt_d, count, gs)
+#define LOOKME_MS_K(DT_, L_)                  \
+  do {                                        \
+    if (k <= 8) LOOKME_MS(DT_, 8, L_);        \
+    else if (k <= 16) LOOKME_MS(DT_, 16, L_); \
+    else LOOKME_MS(DT_, 32, L_);              \
   } while (0)
   if (dt == DT_BF16) {
-    if (scales <= 4) LOOKME_MS_K(DT_BF16, 4);
-    else LOOKME_MS_K(DT_BF16, MS_MAX_SCALES);
+    if (lds) LOOKME_MS_K(DT_BF16, true);
+    else LOOKME_MS_K(DT_BF16, false);
   } else {
-    if (scales <= 4) LOOKME_MS_K(DT_F32, 4);
-    else LOOKME_MS_K(DT_F32, MS_MAX_SCALES);
+    if (lds) LOOKME_MS_K(DT_F32, true);
+    else LOOKME_MS_K(DT_F32, false);
   }
 #undef LOOKME_MS_K
-#undef LOOKME_MS_C
 #undef LOOKME_MS
   return hipGetLastError();
 }
