@@ -42,7 +42,11 @@
 
 namespace lookme {
 
-using TgShape = DtlShape<2, 2, 2, 2, 128>;
+// TI: 16-row MFMA tiles a wave; 2 (64-row tiles), or 1 (32-row tiles) where
+// that spreads a product over CUs that would have no workgroup.
+template <int TI>
+using TgShapeT = DtlShape<2, 2, TI, 2, 128>;
+using TgShape = TgShapeT<2>;
 constexpr int TG_KB = 128;
 
 enum : int {
@@ -81,9 +85,10 @@ struct TileGemmParams {
 // when col_major (so they land on one XCD and share its L2 copy of the B
 // rows, which the larger operand then crosses HBM once), else the column
 // tiles of one row block.
+template <int TI>
 __device__ __forceinline__ void tile_origin(const TileGemmParams& a, int tile, int tcols,
                                             int64_t* m0, int* n0) {
-  constexpr int BM = TgShape::BM;
+  constexpr int BM = TgShapeT<TI>::BM;
   if (a.col_major) {
     const int tiles_m = (int)((a.rows + BM - 1) / BM);
     *m0 = (int64_t)(tile % tiles_m) * BM;
@@ -100,13 +105,13 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.f + expf(-x)); 
 // Epilogue of a tile (tile index `tile` of batch z) from the accumulators of
 // thread tid: the lane holds rows m0 + wm + 16 i + 4 g + r and tile columns
 // wn + 16 j + n16.  xch: 4096 floats of LDS (EPI_SWIGLU only).
-template <int DT, int EPI>
+template <int DT, int EPI, int TI>
 __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
-                                              f32x4_t (&acc)[2][2],
+                                              f32x4_t (&acc)[TI][2],
                                               int64_t z, int tile, int tid, float* xch,
                                               int64_t rows) {
-  using S = TgShape;
-  constexpr int MI = 2, NJ = 2, WN = 2;
+  using S = TgShapeT<TI>;
+  constexpr int MI = TI, NJ = 2, WN = 2;
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
   constexpr int TCOLS = EPI == EPI_SWIGLU ? S::BN / 2 : S::BN;
   const int lane = tid & 63, wv = tid >> 6;
@@ -114,7 +119,7 @@ __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
   const int wm = (wv / WN) * 16 * MI, wn = (wv % WN) * 16 * NJ;
   int64_t m0;
   int n0;
-  tile_origin(a, tile, TCOLS, &m0, &n0);
+  tile_origin<TI>(a, tile, TCOLS, &m0, &n0);
   if constexpr (EPI == EPI_SWIGLU) {
     // the up half (waves with wn = 32) passes its tile through LDS to the
     // gate half (wn = 0) of the same rows
@@ -247,10 +252,10 @@ __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
   }
 }
 
-template <int DT, int EPI, int NS>
+template <int DT, int EPI, int NS, int TI = 2>
 __global__ __launch_bounds__(256) void tile_gemm_kernel(TileGemmParams a) {
-  using S = TgShape;
-  constexpr int MI = 2, NJ = 2, KB = TG_KB, KSL = KB / 64, WN = 2;
+  using S = TgShapeT<TI>;
+  constexpr int MI = TI, NJ = 2, KB = TG_KB, KSL = KB / 64, WN = 2;
   constexpr int TCOLS = EPI == EPI_SWIGLU ? S::BN / 2 : S::BN;   // output columns a tile
   static_assert(NS >= 2, "a stage in flight while one is multiplied");
   __shared__ __attribute__((aligned(1024))) char lds[NS][S::STAGE];
@@ -265,7 +270,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(TileGemmParams a) {
   if (tile < 0) return;
   int64_t m0;
   int n0;
-  tile_origin(a, tile, TCOLS, &m0, &n0);
+  tile_origin<TI>(a, tile, TCOLS, &m0, &n0);
   int64_t rows = a.rows;   // live rows of this batch
   if (a.count != nullptr) {
     const int64_t c = a.count[z * a.count_step];
@@ -394,7 +399,7 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(TileGemmParams a) {
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into LDS outlives the wave
 
-  tile_epilogue<DT, EPI>(a, acc, z, tile, tid, reinterpret_cast<float*>(&lds[0][0]), rows);
+  tile_epilogue<DT, EPI, TI>(a, acc, z, tile, tid, reinterpret_cast<float*>(&lds[0][0]), rows);
 }
 
 // ---------------------------------------------------------------------------
@@ -637,11 +642,32 @@ hipError_t launch_tile_gemm(int dt, TileGemmParams p, int batches, hipStream_t s
   // by the matrix cores on either, and 64 x 64 tiles fill the last round
   // better: from 512 tiles on (16384 x 2048 x 1024 607 -> 561 us; 8192 x 1024
   // x 1024, 128 tiles, 166 and 172).
+  // Short sums (K of at most 1 KiB a row) are over before the deeper pipeline
+  // pays, so they take it where most of a round is whole tiles (relevance
+  // lookups of 20011 rows, 158 tiles, 131.9 us here and 129.1 phased; of
+  // 12000, 94 tiles, 125.2 and 132.2; 4000 x 2048 x 512, 128, 19.0 and 20.5).
   // Its lane offsets are 32-bit: rows below 8 MiB, gathered rows inside 4 GiB.
   const bool near = p.a_bytes < (8 << 20) && p.k_bytes < (8 << 20) && p.b_ld < (8 << 20) &&
                     (p.a_sel == nullptr || p.sel_rows * p.a_bytes < ((int64_t)1 << 32));
-  if (p.cols % 8 == 0 && near && phase_tiles<EPI>(p, batches) >= (dt == DT_BF16 ? 48 : 512))
+  if (p.cols % 8 == 0 && near &&
+      phase_tiles<EPI>(p, batches) >= (dt != DT_BF16 ? 512 : p.k_bytes > 1024 ? 48 : 129))
     return launch_phase<EPI>(dt, p, batches, st);
+  if constexpr (EPI != EPI_SWIGLU) {
+    // 32-row tiles while every one has a CU of its own and 64-row ones leave
+    // half of the CUs idle: a CU's LDS traffic a stage (which bounds these)
+    // falls from 48 to 36 KiB.  Image fused
+      // injection 30.3 -> 27.4 us, propagated 95.7 -> 89.2 (same sums, same bits).
+    const int tiles32 = (int)((p.rows + 31) / 32 * ((p.cols + 63) / 64));
+    if ((int64_t)tiles32 * batches <= 256) {
+      p.tiles = tiles32;
+      const dim3 g((unsigned)((tiles32 + 7) / 8 * 8), (unsigned)batches);
+      if (dt == DT_BF16)
+        hipLaunchKernelGGL((tile_gemm_kernel<DT_BF16, EPI, 8, 1>), g, dim3(256), 0, st, p);
+      else
+        hipLaunchKernelGGL((tile_gemm_kernel<DT_F32, EPI, 8, 1>), g, dim3(256), 0, st, p);
+      return hipGetLastError();
+    }
+  }
   const unsigned gx = (unsigned)((p.tiles + 7) / 8 * 8);
   const dim3 grid(gx, (unsigned)batches);
   const int64_t wgs = (int64_t)gx * batches;
