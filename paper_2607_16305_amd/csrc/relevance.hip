@@ -532,12 +532,15 @@ __global__ __launch_bounds__(256) void relevance_merge_kernel(const uint64_t* __
     }
 }
 
-// Ranges of W2 rows per row block: enough units to fill the chip's 512
-// resident workgroups, each range at least 128 rows (and k), and as many as
-// keep a range's b2 within its LDS space; 0 when that takes more than 16.
-static int relevance_splits(int64_t row_blocks, int P, int k) {
+// Ranges of W2 rows per row block: enough for `units` units (512: the chip's
+// resident workgroups; 256 for the 32 x 32 form, whose list upkeep grows with
+// every range: 12000 rows x 1024, k = 16, 139.8 -> 132.2 us for the
+// whole lookup, 20011 x 1000, k = 8, 129.9 -> 128.4), each range at least 128 rows (and k),
+// and as many as keep a range's b2 within its LDS space; 0 when that takes
+// more than 16.
+static int relevance_splits(int64_t row_blocks, int P, int k, int units = 512) {
   int splits = 1;
-  while (splits < 16 && row_blocks * splits < 512 && P / (2 * splits) >= 128 &&
+  while (splits < 16 && row_blocks * splits < units && P / (2 * splits) >= 128 &&
          P / (2 * splits) >= k)
     splits *= 2;
   while (splits <= 16 && (P + splits - 1) / splits > RT_MAX_KPS) splits *= 2;
@@ -587,7 +590,7 @@ template <int KS, int KL, int WAVES>
 static hipError_t launch_topk32(const RelTopkParams& p0, float* part_ws, hipStream_t st) {
   RelTopkParams p = p0;
   const int64_t row_blocks = (p.rows + 32 * WAVES - 1) / (32 * WAVES);
-  p.splits = relevance_splits(row_blocks, p.P, p.k);
+  p.splits = relevance_splits(row_blocks, p.P, p.k, 256);
   if (p.splits < 1) return hipErrorInvalidValue;
   p.kps = ((p.P + p.splits - 1) / p.splits + 31) / 32 * 32;
   p.splits = (p.P + p.kps - 1) / p.kps;   // no empty range
