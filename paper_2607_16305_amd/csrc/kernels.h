@@ -27,8 +27,8 @@ hipError_t noalloc_scratch(void** out);
 // ---- routing: scene[r] = argmax_s <q_r, K1[s]> + bias[s] over rows r -------
 // Three kernels, by batch size (route_plan):
 //  * ROUTE_DTL: batches of at least ROUTE_DTL_MIN_ROWS rows whose key rows
-//    are whole 128-byte steps: blocks of `rows` (128 or 256) rows x 256-key
-//    tiles on the matrix cores (route.hip), the key tiles of a block split
+//    are whole 128-byte steps: blocks of 128 rows x 256-key tiles on the
+//    matrix cores (route.hip), the key tiles of a block split
 //    over `splits` workgroups of `per_split` tiles;
 //  * ROUTE_STREAM: small batches, 16-row tiles in the scoring kernel's
 //    streaming mode, the keys split over `splits` workgroups of `per_split`
@@ -38,7 +38,7 @@ hipError_t noalloc_scratch(void** out);
 // pairs, `count` ROUTE_COUNTERS arrival counters that are zero before the
 // first call and left at zero by every call.
 constexpr int ROUTE_STREAM = 0, ROUTE_SHARED = 1, ROUTE_DTL = 2;
-constexpr int ROUTE_DTL_KEYS = 256, ROUTE_DTL_MAX_TPS = 16;
+constexpr int ROUTE_DTL_ROWS = 128, ROUTE_DTL_KEYS = 256, ROUTE_DTL_MAX_TPS = 16;
 constexpr int64_t ROUTE_DTL_MIN_ROWS = 4096;
 constexpr int ROUTE_COUNTERS = 4096;
 struct RoutePlan {
@@ -46,11 +46,9 @@ struct RoutePlan {
   int splits;
   int per_split;          // DTL: 256-key tiles; STREAM: keys (a multiple of 64)
   int64_t part_entries;
-  int rows;               // DTL: rows of a block
 };
-// cos: cosine scores, which only the scoring kernel's modes implement; bias:
-// the handle has a scene bias
-RoutePlan route_plan(int64_t rows, int S, int64_t row_bytes, bool cos, bool bias);
+// cos: cosine scores, which only the scoring kernel's modes implement
+RoutePlan route_plan(int64_t rows, int S, int64_t row_bytes, bool cos = false);
 hipError_t launch_route(int dt, const void* q, const void* scene_keys, const float* bias,
                         int32_t* scene, int64_t rows, int d_e, int S, uint64_t* part,
                         int32_t* count, hipStream_t st, bool cos = false);

@@ -84,7 +84,7 @@ constexpr size_t ZEROED_BYTES =
     256 + lookme::ROUTE_COUNTERS * 4 + (size_t)lookme::SPLIT_UNITS * lookme::UNIT_STREAM_ROWS * 4;
 
 Layout layout(const lookme_desc_t& d, int32_t layers, int64_t n, int32_t relevance,
-              int32_t fusion_dff, int32_t scales, bool bias) {
+              int32_t fusion_dff, int32_t scales) {
   const int64_t rows = (int64_t)layers * n;
   const int64_t chunks = lookme::bucket_chunks(rows);
   const int64_t units = lookme::bucket_max_units(rows, d.num_scenes);
@@ -103,7 +103,7 @@ Layout layout(const lookme_desc_t& d, int32_t layers, int64_t n, int32_t relevan
   L.rel_tab = take(relevance ? (size_t)d.num_scenes * relevance * 4 : 0);
   const lookme::RoutePlan plan =
       lookme::route_plan(rows, d.num_scenes, (int64_t)d.key_dim * elem_size(d.dtype),
-                         d.score == LOOKME_SCORE_COS, bias);
+                         d.score == LOOKME_SCORE_COS);
   L.route_part = take((size_t)plan.part_entries * 8);
   L.chunk_hist = take((size_t)chunks * d.num_scenes * 4);
   L.local_rank = take((size_t)rows * 4);
@@ -150,7 +150,7 @@ lookme_status_t check_layers_n(int32_t layers, int64_t n) {
 }
 
 lookme_status_t check_workspace(lookme_t h, int32_t layers, int64_t n, Layout* L) {
-  *L = layout(h->d, layers, n, h->rel.hidden, h->fus.d_ff, h->ms_scales, h->bias != nullptr);
+  *L = layout(h->d, layers, n, h->rel.hidden, h->fus.d_ff, h->ms_scales);
   if (h->ws == nullptr) return fail(LOOKME_ERR_WORKSPACE, "no workspace set");
   if (h->ws_bytes < L->total)
     return fail(LOOKME_ERR_WORKSPACE, "workspace of %zu bytes, %zu needed for %d x %lld rows",
@@ -506,7 +506,7 @@ lookme_status_t lookme_workspace_size(lookme_t h, int32_t layers, int64_t n_toke
   LOOKME_TRY(check_handle(h));
   if (bytes == nullptr) return fail(LOOKME_ERR_INVALID, "bytes is NULL");
   LOOKME_TRY(check_layers_n(layers, n_tokens));
-  *bytes = layout(h->d, layers, n_tokens, h->rel.hidden, h->fus.d_ff, h->ms_scales, h->bias != nullptr).total;
+  *bytes = layout(h->d, layers, n_tokens, h->rel.hidden, h->fus.d_ff, h->ms_scales).total;
   return LOOKME_OK;
 }
 
@@ -706,10 +706,16 @@ lookme_status_t lookme_select(lookme_t h, int32_t layers, int64_t n, int64_t n_k
   LOOKME_TRY(check_ptr(kept_out, "kept_out"));
   Layout L;
   LOOKME_TRY(check_workspace(h, layers, n, &L));
-  // the norms in their background form: lookme_select is the call that runs
-  // beside lookme_route / lookme_lookup on a second stream
+  // lookme_select is the call that runs beside lookme_route / lookme_lookup on
+  // a second stream: the norms in their background form, one workgroup a CU
+  // for long, while the projection of these tokens is one round of 256 x 256
+  // tiles, after which routing runs beside them; a projection of several
+  // rounds (its tiles fill a CU's registers) would wait for each of those
+  // workgroups, and the norms as one short full grid cost it less (four-layer
+  // step 0.792 -> 0.725 ms)
+  const int64_t tiles = (n + 255) / 256 * (((int64_t)layers * h->d.key_dim + 255) / 256);
   return run_select(h, L, layers, n, n_keep, crit, d_c, kept_out, static_cast<hipStream_t>(stream),
-                    true);
+                    tiles <= 256);
 }
 
 lookme_status_t lookme_inject_kept(lookme_t h, int32_t layers, int64_t n, int64_t n_keep,

@@ -3,7 +3,7 @@
 // argmax_s <q_r, K1[s]> + b[s], lowest s on exact ties; the scores are never
 // written to memory.
 //
-// A workgroup owns 64 MI query rows (256 or 128) and a range of 256-key tiles,
+// A workgroup owns 128 query rows and a range of 256-key tiles,
 // computed on the phased loop of phase_gemm.h as one stream of K stages across
 // all of its key tiles.  Each quadrant of a tile's last stage is folded (plus
 // the bias, staged in LDS) into a running best per row while the next
@@ -71,12 +71,12 @@ struct RouteLoads {
   }
 };
 
-template <int DT, bool BIAS, int MI>
+template <int DT, bool BIAS>
 __global__ __launch_bounds__(512, 2) void route_phase_kernel(RouteDtlParams a) {
-  constexpr int NJ = 2;
+  constexpr int MI = 2, NJ = 2;
   using S = PgShape<MI, NJ>;
   constexpr int W = S::W;
-  static_assert(S::BN == ROUTE_DTL_KEYS, "key tiles");
+  static_assert(S::BM == ROUTE_DTL_ROWS && S::BN == ROUTE_DTL_KEYS, "tile shape");
   // All of the kernel's LDS is one object.  With several __shared__ objects
   // the compiler tags their accesses with alias scopes and then, finding the
   // stage buffers' direct-to-LDS loads and fragment reads in one scope, puts
@@ -86,8 +86,7 @@ __global__ __launch_bounds__(512, 2) void route_phase_kernel(RouteDtlParams a) {
   constexpr int BIAS_OFF = 2 * S::BUF;
   constexpr int BIAS_BYTES = BIAS ? ROUTE_DTL_MAX_TPS * S::BN * 4 : 0;
   static_assert(4 * S::BM * 8 + 16 <= 2 * S::BUF, "merge arrays in the stage buffers");
-  constexpr int BEST_OFF = BIAS_OFF + BIAS_BYTES;
-  __shared__ __attribute__((aligned(1024))) char smem[BEST_OFF + 2 * MI * 512 * 8];
+  __shared__ __attribute__((aligned(1024))) char smem[BIAS_OFF + BIAS_BYTES];
   float* s_bias = reinterpret_cast<float*>(smem + BIAS_OFF);
   float (*m_s)[S::BM] = reinterpret_cast<float (*)[S::BM]>(smem);
   int (*m_i)[S::BM] = reinterpret_cast<int (*)[S::BM]>(smem + 4 * S::BM * 4);
@@ -139,16 +138,17 @@ __global__ __launch_bounds__(512, 2) void route_phase_kernel(RouteDtlParams a) {
     }
   }
 
-  // running best of the lane's 2 MI rows, in LDS words of its own between
-  // the folds (in registers beside the accumulators and fragments they made
-  // the loop spill, and every reload waits for the stage loads before it)
-  float* ls = reinterpret_cast<float*>(smem + BEST_OFF) + tid;
-  int* li = reinterpret_cast<int*>(smem + BEST_OFF + 2 * MI * 512 * 4) + tid;
+  // running best of the lane's 2 MI rows (256-row blocks had no registers for
+  // them: the loop spilled, and every reload waited for the loads before it)
+  float bs[2][MI];
+  int bi[2][MI];
 #pragma unroll
-  for (int x = 0; x < 2 * MI; ++x) {
-    ls[x * 512] = -__builtin_inff();
-    li[x * 512] = -1;
-  }
+  for (int qi = 0; qi < 2; ++qi)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      bs[qi][i] = -__builtin_inff();
+      bi[qi][i] = -1;
+    }
   f32x4_t acc[2][2][MI][NJ];
   int c_tile = 0, c_ks = 0;   // the stage that is multiplied
   // a quadrant of a complete tile: the lane holds W neighbouring keys of its
@@ -172,8 +172,8 @@ __global__ __launch_bounds__(512, 2) void route_phase_kernel(RouteDtlParams a) {
     }
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      float b = ls[(qi * MI + i) * 512];
-      int k = li[(qi * MI + i) * 512];
+      float b = bs[qi][i];
+      int k = bi[qi][i];
 #pragma unroll
       for (int e = 0; e < W; ++e) {
         float v = acc[qi][qj][i][e >> 2][e & 3];
@@ -182,8 +182,8 @@ __global__ __launch_bounds__(512, 2) void route_phase_kernel(RouteDtlParams a) {
         k = take ? key0 + e : k;
         b = fmaxf(b, v);
       }
-      ls[(qi * MI + i) * 512] = b;
-      li[(qi * MI + i) * 512] = k;
+      bs[qi][i] = b;
+      bi[qi][i] = k;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) acc[qi][qj][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
@@ -201,15 +201,6 @@ __global__ __launch_bounds__(512, 2) void route_phase_kernel(RouteDtlParams a) {
       c_ks = end ? 0 : c_ks + 1;
     }
   });
-  float bs[2][MI];
-  int bi[2][MI];
-#pragma unroll
-  for (int qi = 0; qi < 2; ++qi)
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      bs[qi][i] = ls[(qi * MI + i) * 512];
-      bi[qi][i] = li[(qi * MI + i) * 512];
-    }
   __syncthreads();   // every wave is done with the stage buffers
 
   // merge the 4 lanes of a row (keys W g of every tile half), then the 4
@@ -253,18 +244,6 @@ __global__ __launch_bounds__(512, 2) void route_phase_kernel(RouteDtlParams a) {
                        nr, best_s, best_i, s_last);
 }
 
-template <int DT, bool BIAS>
-static void launch_mi(const RoutePlan& plan, const RouteDtlParams& p, hipStream_t st) {
-  const dim3 grid((unsigned)((p.units + 7) / 8 * 8));
-  if constexpr (!BIAS) {   // with a bias table 256 rows need more LDS than there is
-    if (plan.rows == 256) {
-      hipLaunchKernelGGL((route_phase_kernel<DT, BIAS, 4>), grid, dim3(512), 0, st, p);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((route_phase_kernel<DT, BIAS, 2>), grid, dim3(512), 0, st, p);
-}
-
 hipError_t launch_route_dtl(int dt, const void* q, const void* scene_keys, const float* bias,
                             int32_t* scene, int64_t rows, int d_e, int S, const RoutePlan& plan,
                             uint64_t* part, int32_t* count, hipStream_t st) {
@@ -277,16 +256,17 @@ hipError_t launch_route_dtl(int dt, const void* q, const void* scene_keys, const
   p.S = S;
   p.splits = plan.splits;
   p.tps = plan.per_split;
-  p.units = (int)((rows + plan.rows - 1) / plan.rows * plan.splits);
+  p.units = (int)((rows + ROUTE_DTL_ROWS - 1) / ROUTE_DTL_ROWS * plan.splits);
   p.scene = scene;
   p.part = part;
   p.count = count;
+  const dim3 grid((unsigned)((p.units + 7) / 8 * 8));
   if (dt == DT_BF16) {
-    if (bias != nullptr) launch_mi<DT_BF16, true>(plan, p, st);
-    else launch_mi<DT_BF16, false>(plan, p, st);
+    if (bias != nullptr) hipLaunchKernelGGL((route_phase_kernel<DT_BF16, true>), grid, dim3(512), 0, st, p);
+    else hipLaunchKernelGGL((route_phase_kernel<DT_BF16, false>), grid, dim3(512), 0, st, p);
   } else {
-    if (bias != nullptr) launch_mi<DT_F32, true>(plan, p, st);
-    else launch_mi<DT_F32, false>(plan, p, st);
+    if (bias != nullptr) hipLaunchKernelGGL((route_phase_kernel<DT_F32, true>), grid, dim3(512), 0, st, p);
+    else hipLaunchKernelGGL((route_phase_kernel<DT_F32, false>), grid, dim3(512), 0, st, p);
   }
   return hipGetLastError();
 }

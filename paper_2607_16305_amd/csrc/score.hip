@@ -867,47 +867,43 @@ static int route_unit_rows(int64_t rows, int shared_rows) {
 
 static int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-// Rows per block and key ranges per row block of the tile kernel, which runs
-// one workgroup a CU: the choice with the least time by a fit to measured
-// times (bf16, 1 KiB keys): a round of 256 units takes 1.69 us a K stage of
-// 256 x 256 and 6 us for its first loads and its end (128 x 256: 1.05 and
-// 4), and 3 us more where the ranges of a block are merged.  Measured, best
-// plans of 256- and of 128-row blocks: 32768 rows x 4096 keys 149.8 (two
-// ranges) and 150.3 us, 92160 x 1024 111.6 and 111.9, 46080 x 4096 199.8
-// (four ranges) and 219, 60000 x 300 36.1 and 40.7, 20000 x 500 21.9 and
-// 20.5, 8192 x 1024 22.2 and 17.6 (four ranges), 4096 x 256 18.3 and 11.4.
-// The kernel before (three-stage ring, 128-row blocks) at its best plans:
-// 159.6, 116.6, 212, 45.3, 21.1, 20.2, 13.7; the scoring kernel's shared mode
-// 169 at 92160 x 1024.  A unit's bias table holds ROUTE_DTL_MAX_TPS tiles
-// (and leaves no LDS for 256-row blocks), and split blocks have an arrival
-// counter each.
-static RoutePlan route_tile_plan(int64_t rows, int S, int64_t row_bytes, bool bias) {
-  RoutePlan best{ROUTE_DTL, 0, 0, 0, 0};
+// Key ranges per 128-row block of the tile kernel, which runs one workgroup a
+// CU: the split with the least time by a fit to measured times (bf16, 1 KiB
+// keys): a round of 256 units takes 1.05 us a K stage and 4 us for its first
+// loads and its end, and 3 us more where the ranges of a block are merged.
+// Measured at the best split: 32768 rows x 4096 keys 150.3 us, 23040 x 1024
+// 36.2, 92160 x 1024 111.9, 46080 x 4096 219 (two ranges), 60000 x 300 40.7,
+// 20000 x 500 20.5, 8192 x 1024 17.6 (four ranges), 4096 x 256 11.4.  The
+// kernel before (three-stage ring) at its best splits: 159.6, 36.7, 116.6,
+// 212, 45.3, 21.1, 20.2, 13.7; the scoring kernel's shared mode 169 at
+// 92160 x 1024.  (256-row blocks measured 149.8, 36.6, 111.6, 199.8, 36.1,
+// 21.9, 22.2, 18.3, but fill a CU's registers and LDS: nothing of another
+// stream runs beside them.)  A unit's bias table holds ROUTE_DTL_MAX_TPS
+// tiles, and split blocks have an arrival counter each.
+static RoutePlan route_tile_plan(int64_t rows, int S, int64_t row_bytes) {
+  RoutePlan best{ROUTE_DTL, 0, 0, 0};
   const int tiles = cdiv(S, ROUTE_DTL_KEYS);
+  const int64_t blocks = (rows + ROUTE_DTL_ROWS - 1) / ROUTE_DTL_ROWS;
   double least = 0.;
-  for (int br = bias ? 128 : 256; br >= 128; br /= 2) {
-    const int64_t blocks = (rows + br - 1) / br;
-    const double stage = br == 256 ? 1.69 : 1.05, unit = br == 256 ? 6. : 4.;
-    for (int sp = 1; sp < 2 * tiles; sp *= 2) {
-      const int tps = cdiv(tiles, sp), n = cdiv(tiles, tps);
-      if (tps > ROUTE_DTL_MAX_TPS || (n > 1 && blocks > ROUTE_COUNTERS)) continue;
-      const double t = (double)cdiv(blocks * n, 256) *
-                       (tps * (double)(row_bytes / 128) * stage + unit + (n > 1 ? 3. : 0.));
-      if (best.splits == 0 || t < least) {
-        least = t;
-        best = RoutePlan{ROUTE_DTL, n, tps, n > 1 ? blocks * n * br : 0, br};
-      }
+  for (int sp = 1; sp < 2 * tiles; sp *= 2) {
+    const int tps = cdiv(tiles, sp), n = cdiv(tiles, tps);
+    if (tps > ROUTE_DTL_MAX_TPS || (n > 1 && blocks > ROUTE_COUNTERS)) continue;
+    const double t = (double)cdiv(blocks * n, 256) *
+                     (tps * (double)(row_bytes / 128) * 1.05 + 4. + (n > 1 ? 3. : 0.));
+    if (best.splits == 0 || t < least) {
+      least = t;
+      best = RoutePlan{ROUTE_DTL, n, tps, n > 1 ? blocks * n * ROUTE_DTL_ROWS : 0};
     }
   }
   return best;
 }
 
-RoutePlan route_plan(int64_t rows, int S, int64_t row_bytes, bool cos, bool bias) {
-  RoutePlan p{ROUTE_SHARED, 1, S, 0, 0};
+RoutePlan route_plan(int64_t rows, int S, int64_t row_bytes, bool cos) {
+  RoutePlan p{ROUTE_SHARED, 1, S, 0};
   if (rows <= 0 || S <= 0) return p;
   // the tile kernel scores dot products only
   if (!cos && rows >= ROUTE_DTL_MIN_ROWS && row_bytes % 128 == 0) {
-    const RoutePlan t = route_tile_plan(rows, S, row_bytes, bias);
+    const RoutePlan t = route_tile_plan(rows, S, row_bytes);
     if (t.splits > 0) return t;
   }
   if (route_unit_rows(rows, shared_unit_rows(row_bytes, 0)) == UNIT_STREAM_ROWS) {
@@ -945,7 +941,7 @@ hipError_t launch_route(int dt, const void* q, const void* scene_keys, const flo
   p.route_rows = route_unit_rows(rows, shared_unit_rows(p.row_bytes, 0));
   p.out_idx = scene;
   p.cos = cos ? 1 : 0;
-  const RoutePlan plan = route_plan(rows, S, p.row_bytes, cos, bias != nullptr);
+  const RoutePlan plan = route_plan(rows, S, p.row_bytes, cos);
   if (plan.mode == ROUTE_DTL)
     return launch_route_dtl(dt, q, scene_keys, bias, scene, rows, d_e, S, plan, part, count, st);
   p.route_rows = plan.mode == ROUTE_STREAM ? UNIT_STREAM_ROWS : p.route_rows;
