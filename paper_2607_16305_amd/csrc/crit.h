@@ -233,7 +233,18 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
   const int per = ((n + 63) / 64 + WAVES - 1) / WAVES * 64;
   const int w0 = wv * per, w1 = w0 + per < n ? w0 + per : n;
   auto each = [&](auto&& f) {
-    for (int i = w0 + lane; i < w1; i += WAVE) f(i, CACHED ? cache[i] : gkey[i]);
+    if constexpr (CACHED) {
+      for (int i = w0 + lane; i < w1; i += WAVE) f(i, cache[i]);
+    } else {
+      for (int j = w0 + lane; j < w1; j += WAVE * BATCH) {
+        uint32_t v[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) v[u] = gkey[j + u * WAVE < w1 ? j + u * WAVE : w1 - 1];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+          if (j + u * WAVE < w1) f(j + u * WAVE, v[u]);
+      }
+    }
   };
 
   // ---- radix select (MSB first, 8 bits a pass): the n_keep-th largest T ----

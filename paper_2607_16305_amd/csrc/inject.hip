@@ -42,15 +42,15 @@ __global__ __launch_bounds__(NORM_WAVES * WAVE) void crit_norm_kernel(
   }
 }
 
-template <int CN>
-__global__ __launch_bounds__(SEL_THREADS) void crit_select_kernel(
+template <int CN, int THREADS = SEL_THREADS>
+__global__ __launch_bounds__(THREADS) void crit_select_kernel(
     const uint32_t* __restrict__ key_all, int64_t n, int64_t n_keep,
     int32_t* __restrict__ kept_all) {
   __shared__ uint32_t cache[sel_cache_words(CN)];
   __shared__ SelLds sl;
   const int layer = blockIdx.x;
-  select_layer<CN>(key_all + (int64_t)layer * n, n, n_keep, kept_all + (int64_t)layer * n_keep,
-                   cache, sl);
+  select_layer<CN, THREADS>(key_all + (int64_t)layer * n, n, n_keep,
+                            kept_all + (int64_t)layer * n_keep, cache, sl);
 }
 
 // Rows of the injections whose kept id, scene or primitive index lay outside
@@ -426,9 +426,16 @@ hipError_t launch_crit_norm(int dt, int64_t rows, const void* crit, int d_c, uin
 }
 
 hipError_t launch_crit_select(int layers, int64_t n, int64_t n_keep, const uint32_t* key,
-                              int32_t* kept, hipStream_t st) {
+                              int32_t* kept, hipStream_t st, bool background) {
   if (n == 0 || n_keep == 0) return hipSuccess;
-  if (n <= SEL_CACHE_SMALL)
+  // beside the projection and routing of a second stream the large cache's
+  // 132 KiB (and 16 waves) find no CU before those have ended, and the select
+  // then runs into Level-2's start: 8 waves reading the keys from L2 fit
+  // beside them (step of 32768 tokens 2.23 -> 2.17 ms)
+  if (background && n > SEL_CACHE_SMALL)
+    hipLaunchKernelGGL((crit_select_kernel<0, SEL_THREADS / 2>), dim3(layers),
+                       dim3(SEL_THREADS / 2), 0, st, key, n, n_keep, kept);
+  else if (n <= SEL_CACHE_SMALL)
     hipLaunchKernelGGL(crit_select_kernel<SEL_CACHE_SMALL>, dim3(layers), dim3(SEL_THREADS), 0, st,
                        key, n, n_keep, kept);
   else if (n <= SEL_CACHE_N)

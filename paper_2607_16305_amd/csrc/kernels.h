@@ -228,7 +228,7 @@ hipError_t launch_lookup(int dt, const void* q, const void* prim_keys, const Buc
 hipError_t launch_crit_norm(int dt, int64_t rows, const void* crit, int d_c, uint32_t* key,
                             hipStream_t st, bool background = false);
 hipError_t launch_crit_select(int layers, int64_t n, int64_t n_keep, const uint32_t* key,
-                              int32_t* kept, hipStream_t st);
+                              int32_t* kept, hipStream_t st, bool background = false);
 // The injections' count of rows with an index out of range (see
 // inject_kernel), read and reset on `st` (synchronising it).
 hipError_t take_index_errors(hipStream_t st, uint64_t* out);

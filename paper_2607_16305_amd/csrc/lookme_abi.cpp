@@ -281,7 +281,7 @@ lookme_status_t run_select(lookme_t h, const Layout& L, int32_t layers, int64_t 
   }
   if (n_keep == 0) return LOOKME_OK;
   Timed tm(h, LOOKME_GROUP_SELECT, st);
-  return hip_status(lookme::launch_crit_select(layers, n, n_keep, key, kept, st),
+  return hip_status(lookme::launch_crit_select(layers, n, n_keep, key, kept, st, background),
                     "select launch");
 }
 
