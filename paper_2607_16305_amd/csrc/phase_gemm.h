@@ -129,8 +129,8 @@ struct PgLoop {
   // one stage; fb0 holds B0(s), fb1 receives B1(s) and then B0(s + 1)
   // (before phase k the part it reads is the oldest of the seven loaded
   // last: the six younger ones may be in flight).  done(q): quadrant q
-  // (2 qi + qj) of the stage has been multiplied; called in the next phase,
-  // beside its products, and for the last one at the end.
+  // (2 qi + qj) of the stage has been multiplied; called in order of q, beside
+  // the products of the phase after it or (2 and 3) at the end.
   template <class Ld, class Done>
   __device__ __forceinline__ void stage(int s, Ld& ld, f32x4_t (&acc)[2][2][MI][NJ],
                                         u32x4_t (&fa0)[2][MI], u32x4_t (&fa1)[2][MI],
@@ -156,8 +156,8 @@ struct PgLoop {
     ld.next();
     ld.a(0, s + 3, a_dst(0, s + 3));
     mma(fa1, fb0, acc[1][0]);
-    done(3);
     done(2);
+    done(3);
   }
 
   // done(s, q): see stage
