@@ -33,14 +33,15 @@ hipError_t noalloc_scratch(void** out);
 //  * ROUTE_STREAM: small batches, 16-row tiles in the scoring kernel's
 //    streaming mode, the keys split over `splits` workgroups of `per_split`
 //    keys;
-//  * ROUTE_SHARED: the scoring kernel's shared mode (64- or 128-row units).
+//  * ROUTE_SHARED: the scoring kernel's shared mode (64- or 128-row units), for
+//    what the others do not take and for many rows over few scenes.
 // Split work meets in route_partial: `part` holds part_entries (scene, score)
 // pairs, `count` ROUTE_COUNTERS arrival counters that are zero before the
 // first call and left at zero by every call.
 constexpr int ROUTE_STREAM = 0, ROUTE_SHARED = 1, ROUTE_DTL = 2;
 constexpr int ROUTE_DTL_ROWS = 128, ROUTE_DTL_KEYS = 256, ROUTE_DTL_MAX_TPS = 16;
 constexpr int64_t ROUTE_DTL_MIN_ROWS = 4096;
-constexpr int ROUTE_COUNTERS = 4096;
+constexpr int ROUTE_COUNTERS = 4096, ROUTE_SHARED_BLOCKS = 512;
 struct RoutePlan {
   int mode;
   int splits;
@@ -48,7 +49,7 @@ struct RoutePlan {
   int64_t part_entries;
 };
 // cos: cosine scores, which only the scoring kernel's modes implement
-RoutePlan route_plan(int64_t rows, int S, int64_t row_bytes, bool cos = false);
+RoutePlan route_plan(int dt, int64_t rows, int S, int64_t row_bytes, bool cos);
 hipError_t launch_route(int dt, const void* q, const void* scene_keys, const float* bias,
                         int32_t* scene, int64_t rows, int d_e, int S, uint64_t* part,
                         int32_t* count, hipStream_t st, bool cos = false);

@@ -102,7 +102,7 @@ Layout layout(const lookme_desc_t& d, int32_t layers, int64_t n, int32_t relevan
   // calls: at an offset that does not depend on the batch
   L.rel_tab = take(relevance ? (size_t)d.num_scenes * relevance * 4 : 0);
   const lookme::RoutePlan plan =
-      lookme::route_plan(rows, d.num_scenes, (int64_t)d.key_dim * elem_size(d.dtype),
+      lookme::route_plan(d.dtype, rows, d.num_scenes, (int64_t)d.key_dim * elem_size(d.dtype),
                          d.score == LOOKME_SCORE_COS);
   L.route_part = take((size_t)plan.part_entries * 8);
   L.chunk_hist = take((size_t)chunks * d.num_scenes * 4);

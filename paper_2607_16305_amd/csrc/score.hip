@@ -868,43 +868,80 @@ static int route_unit_rows(int64_t rows, int shared_rows) {
 static int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // Key ranges per 128-row block of the tile kernel, which runs one workgroup a
-// CU: the split with the least time by a fit to measured times (bf16, 1 KiB
-// keys): a round of 256 units takes 1.05 us a K stage and 4 us for its first
-// loads and its end, and 3 us more where the ranges of a block are merged.
-// Measured at the best split: 32768 rows x 4096 keys 150.3 us, 23040 x 1024
-// 36.2, 92160 x 1024 111.9, 46080 x 4096 219 (two ranges), 60000 x 300 40.7,
-// 20000 x 500 20.5, 8192 x 1024 17.6 (four ranges), 4096 x 256 11.4.  The
-// kernel before (three-stage ring) at its best splits: 159.6, 36.7, 116.6,
-// 212, 45.3, 21.1, 20.2, 13.7; the scoring kernel's shared mode 169 at
-// 92160 x 1024.  (256-row blocks measured 149.8, 36.6, 111.6, 199.8, 36.1,
-// 21.9, 22.2, 18.3, but fill a CU's registers and LDS: nothing of another
-// stream runs beside them.)  A unit's bias table holds ROUTE_DTL_MAX_TPS
-// tiles, and split blocks have an arrival counter each.
-static RoutePlan route_tile_plan(int64_t rows, int S, int64_t row_bytes) {
+// CU: the split with the least time by a fit to measured times.  A round of
+// 256 units takes, in bf16 (float32), 0.8 us (3.77) a K stage and 0.9 (0.7) a
+// key tile for the fold, 2 (2.5) for its first loads and its end, and 3.5
+// more where the ranges of a block are merged.  Measured, split in 1 / 2 / 4 /
+// 8: bf16 50000 rows x 1024 scenes x 512 61.4 / 78.2 / 89.8, 12000 x 4096 x
+// 512 109.8 / 60.2 / 66.9 / 65.1, 8192 x 1024 x 64 10.3 / 9.9 / 11.0; float32
+// 20000 x 4096 x 256 500 / 506 / 391 / 346, 80000 x 1024 x 256 382 / 342 / 372.
+// (256-row blocks fill a CU's registers and LDS: nothing of another stream
+// runs beside them.)  A unit's bias table holds ROUTE_DTL_MAX_TPS tiles, split
+// blocks have an arrival counter each.
+static RoutePlan route_tile_plan(int64_t rows, int S, int64_t row_bytes, bool f32,
+                                 double* us = nullptr) {
   RoutePlan best{ROUTE_DTL, 0, 0, 0};
   const int tiles = cdiv(S, ROUTE_DTL_KEYS);
   const int64_t blocks = (rows + ROUTE_DTL_ROWS - 1) / ROUTE_DTL_ROWS;
+  const double tile = (f32 ? 3.77 : 0.8) * (double)(row_bytes / 128) + (f32 ? 0.7 : 0.9);
   double least = 0.;
   for (int sp = 1; sp < 2 * tiles; sp *= 2) {
     const int tps = cdiv(tiles, sp), n = cdiv(tiles, tps);
     if (tps > ROUTE_DTL_MAX_TPS || (n > 1 && blocks > ROUTE_COUNTERS)) continue;
     const double t = (double)cdiv(blocks * n, 256) *
-                     (tps * (double)(row_bytes / 128) * 1.05 + 4. + (n > 1 ? 3. : 0.));
+                     (tps * tile + (f32 ? 2.5 : 2.) + (n > 1 ? 3.5 : 0.));
     if (best.splits == 0 || t < least) {
       least = t;
       best = RoutePlan{ROUTE_DTL, n, tps, n > 1 ? blocks * n * ROUTE_DTL_ROWS : 0};
     }
   }
+  if (us != nullptr) *us = least;
   return best;
 }
 
-RoutePlan route_plan(int64_t rows, int S, int64_t row_bytes, bool cos) {
+// The scoring kernel's shared mode over the same rows, by a fit to measured
+// times like the one above (both leave out the same few us of a launch).  It
+// walks single scenes where the tile kernel takes 256 at a time, and so wins
+// where most of a tile would be empty: bf16 131072 rows x 300 scenes x 128
+// 20.3 us against 32.8, 400000 x 64 x 64 18.5 and 59.4; with whole tiles the
+// tile kernel does: 131072 x 256 x 256 35.2 and 28.1, x 4096 x 256 378 and 261.
+// A key costs `key` us a `wave` of rows (whole waves up to the second, float32
+// half ones; short bf16 keys fill the chip with 131072 rows); row lengths
+// that are not compiled run the longest one's steps.
+static double route_shared_us(int64_t rows, int S, int64_t row_bytes, bool f32) {
+  const int st = (int)(row_bytes / 128);
+  const double r = (double)rows / 65536.;
+  auto whole = [](double x) { return (double)(int64_t)(x + 0.999999); };
+  double key, wave = r, load;
+  if (f32) {
+    key = st == 2 ? 0.077 : st == 4 ? 0.135 : st == 8 ? 0.262 : 0.63;
+    if (r <= 3.5) wave = whole(2. * r) / 2.;
+    load = 0.6;
+  } else if (st <= 2) {
+    key = st == 1 ? 0.0335 : 0.0415;
+    wave = r <= 4. ? whole(r / 2.) : r / 2.;
+    load = 0.6;
+  } else {
+    key = st == 4 ? 0.044 : st == 8 ? 0.072 : 0.25;
+    if (st == 8) wave = r <= 2. ? whole(r) : r + 0.5;
+    load = st <= 8 ? 1.25 : 2.;
+  }
+  return key * wave * S + load * st * r;
+}
+
+RoutePlan route_plan(int dt, int64_t rows, int S, int64_t row_bytes, bool cos) {
   RoutePlan p{ROUTE_SHARED, 1, S, 0};
   if (rows <= 0 || S <= 0) return p;
   // the tile kernel scores dot products only
   if (!cos && rows >= ROUTE_DTL_MIN_ROWS && row_bytes % 128 == 0) {
-    const RoutePlan t = route_tile_plan(rows, S, row_bytes);
-    if (t.splits > 0) return t;
+    const bool f32 = dt != DT_BF16;
+    double us = 0.;
+    const RoutePlan t = route_tile_plan(rows, S, row_bytes, f32, &us);
+    // below ROUTE_SHARED_BLOCKS blocks the shared mode's units do not fill the
+    // chip
+    if (t.splits > 0 && (rows <= (int64_t)(ROUTE_SHARED_BLOCKS - 1) * ROUTE_DTL_ROWS ||
+                         us <= route_shared_us(rows, S, row_bytes, f32)))
+      return t;
   }
   if (route_unit_rows(rows, shared_unit_rows(row_bytes, 0)) == UNIT_STREAM_ROWS) {
     // small batch: split the keys of every 16-row tile (at least 64 keys a
@@ -941,7 +978,7 @@ hipError_t launch_route(int dt, const void* q, const void* scene_keys, const flo
   p.route_rows = route_unit_rows(rows, shared_unit_rows(p.row_bytes, 0));
   p.out_idx = scene;
   p.cos = cos ? 1 : 0;
-  const RoutePlan plan = route_plan(rows, S, p.row_bytes, cos);
+  const RoutePlan plan = route_plan(dt, rows, S, p.row_bytes, cos);
   if (plan.mode == ROUTE_DTL)
     return launch_route_dtl(dt, q, scene_keys, bias, scene, rows, d_e, S, plan, part, count, st);
   p.route_rows = plan.mode == ROUTE_STREAM ? UNIT_STREAM_ROWS : p.route_rows;

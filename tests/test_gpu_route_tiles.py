@@ -2,9 +2,10 @@
 queries, keys and biases (every score exact, many exact ties, the lowest scene
 wins), at the sizes where the tile kernel can go wrong: fewer scenes than a
 key tile, ragged last tiles and row blocks, one and several key tiles a
-workgroup, split and unsplit ranges, 128- and 256-row blocks, one K stage and
-several; and projections of the middle sizes, on either side of the rule that
-gives them 64 x 64 tiles."""
+workgroup, split and unsplit ranges, one K stage and several, and on either
+side of the rule that gives many rows over few scenes to the scoring kernel;
+and projections of the middle sizes, on either side of the rule that gives
+them 64 x 64 tiles."""
 
 import pytest
 import torch
@@ -19,6 +20,9 @@ CASES = [
     (5000, 257, 64, False), (9001, 700, 192, False), (23040, 1024, 64, False),
     (33000, 1000, 128, False), (40000, 4100, 64, False), (70001, 513, 64, False),
     (4100, 300, 64, True), (23040, 1024, 64, True), (40000, 5000, 64, True),
+    # the scoring kernel's shared mode from 65409 rows, the tile kernel below
+    (65408, 64, 128, False), (65409, 64, 128, True), (70001, 300, 64, False),
+    (66000, 300, 256, True),
 ]
 
 
@@ -69,3 +73,4 @@ def test_projection_of_middle_sizes(n, layers, d_e, d_in):
     torch.cuda.synchronize()
     want = torch.stack([x.float() @ wt[l].float().T for l in range(layers)])
     assert torch.equal(q, want.to(dt))   # |sums| < 256: bf16 holds them exactly
+
