@@ -41,7 +41,7 @@ hipError_t noalloc_scratch(void** out);
 constexpr int ROUTE_STREAM = 0, ROUTE_SHARED = 1, ROUTE_DTL = 2;
 constexpr int ROUTE_DTL_ROWS = 128, ROUTE_DTL_KEYS = 256, ROUTE_DTL_MAX_TPS = 16;
 constexpr int64_t ROUTE_DTL_MIN_ROWS = 4096;
-constexpr int ROUTE_COUNTERS = 4096, ROUTE_SHARED_BLOCKS = 512;
+constexpr int ROUTE_COUNTERS = 4096, ROUTE_SPLIT_UNITS = 2048, ROUTE_SHARED_BLOCKS = 512;
 struct RoutePlan {
   int mode;
   int splits;
@@ -50,6 +50,7 @@ struct RoutePlan {
 };
 // cos: cosine scores, which only the scoring kernel's modes implement
 RoutePlan route_plan(int dt, int64_t rows, int S, int64_t row_bytes, bool cos);
+int64_t route_part_most(int64_t rows, int S, int64_t row_bytes, bool cos);
 hipError_t launch_route(int dt, const void* q, const void* scene_keys, const float* bias,
                         int32_t* scene, int64_t rows, int d_e, int S, uint64_t* part,
                         int32_t* count, hipStream_t st, bool cos = false);

@@ -70,7 +70,11 @@ inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 constexpr int32_t MAX_SCENES = 16384;   // bucketing keeps one histogram per chunk in LDS
 
-// Workspace layout for `layers` x `n` rows.
+// Workspace layout for `layers` x `n` rows: what one call of that size needs
+// (most = false), or a size that no smaller call exceeds (most = true, for
+// lookme_workspace_size: a workspace for a batch serves every smaller one; the
+// partials of a split routing, whose splits fall and rise with the batch, are
+// the one part that would not).
 struct Layout {
   size_t chunk_hist, local_rank, offsets, perm, unit_scene, unit_begin, unit_count, route_count,
       route_part, split_row, split_part, crit_key, kept, rel_tab, rel_logits, fus_r, fus_u, ms_q,
@@ -84,7 +88,7 @@ constexpr size_t ZEROED_BYTES =
     256 + lookme::ROUTE_COUNTERS * 4 + (size_t)lookme::SPLIT_UNITS * lookme::UNIT_STREAM_ROWS * 4;
 
 Layout layout(const lookme_desc_t& d, int32_t layers, int64_t n, int32_t relevance,
-              int32_t fusion_dff, int32_t scales) {
+              int32_t fusion_dff, int32_t scales, bool most = false) {
   const int64_t rows = (int64_t)layers * n;
   const int64_t chunks = lookme::bucket_chunks(rows);
   const int64_t units = lookme::bucket_max_units(rows, d.num_scenes);
@@ -101,10 +105,11 @@ Layout layout(const lookme_desc_t& d, int32_t layers, int64_t n, int32_t relevan
   // the relevance MLP's per-scene table [S, hidden] float32, kept across
   // calls: at an offset that does not depend on the batch
   L.rel_tab = take(relevance ? (size_t)d.num_scenes * relevance * 4 : 0);
-  const lookme::RoutePlan plan =
-      lookme::route_plan(d.dtype, rows, d.num_scenes, (int64_t)d.key_dim * elem_size(d.dtype),
-                         d.score == LOOKME_SCORE_COS);
-  L.route_part = take((size_t)plan.part_entries * 8);
+  const int64_t key_bytes = (int64_t)d.key_dim * elem_size(d.dtype);
+  const bool cos = d.score == LOOKME_SCORE_COS;
+  L.route_part = take((size_t)(most ? lookme::route_part_most(rows, d.num_scenes, key_bytes, cos)
+                                    : lookme::route_plan(d.dtype, rows, d.num_scenes, key_bytes,
+                                                         cos).part_entries) * 8);
   L.chunk_hist = take((size_t)chunks * d.num_scenes * 4);
   L.local_rank = take((size_t)rows * 4);
   L.offsets = take(((size_t)d.num_scenes + 1) * 4);
@@ -508,7 +513,8 @@ lookme_status_t lookme_workspace_size(lookme_t h, int32_t layers, int64_t n_toke
   LOOKME_TRY(check_handle(h));
   if (bytes == nullptr) return fail(LOOKME_ERR_INVALID, "bytes is NULL");
   LOOKME_TRY(check_layers_n(layers, n_tokens));
-  *bytes = layout(h->d, layers, n_tokens, h->rel.hidden, h->fus.d_ff, h->ms_scales).total;
+  *bytes =
+      layout(h->d, layers, n_tokens, h->rel.hidden, h->fus.d_ff, h->ms_scales, true).total;
   return LOOKME_OK;
 }
 

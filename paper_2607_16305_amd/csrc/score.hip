@@ -30,6 +30,8 @@
 // gives 0.  No extra load, so the load pipelines are those of the dot form.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "crit.h"
 #include "dtl.h"
@@ -877,17 +879,27 @@ static int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // 20000 x 4096 x 256 500 / 506 / 391 / 346, 80000 x 1024 x 256 382 / 342 / 372.
 // (256-row blocks fill a CU's registers and LDS: nothing of another stream
 // runs beside them.)  A unit's bias table holds ROUTE_DTL_MAX_TPS tiles, split
-// blocks have an arrival counter each.
+// blocks have an arrival counter each, and splits beyond the first that holds
+// the bias table make at most ROUTE_SPLIT_UNITS units.
+static int route_first_split(int tiles) {
+  int sp = 1;
+  while (cdiv(tiles, sp) > ROUTE_DTL_MAX_TPS) sp *= 2;
+  return sp;
+}
+static int route_ranges(int tiles, int sp) { return cdiv(tiles, cdiv(tiles, sp)); }
+
 static RoutePlan route_tile_plan(int64_t rows, int S, int64_t row_bytes, bool f32,
                                  double* us = nullptr) {
   RoutePlan best{ROUTE_DTL, 0, 0, 0};
   const int tiles = cdiv(S, ROUTE_DTL_KEYS);
+  const int first = route_first_split(tiles);
   const int64_t blocks = (rows + ROUTE_DTL_ROWS - 1) / ROUTE_DTL_ROWS;
   const double tile = (f32 ? 3.77 : 0.8) * (double)(row_bytes / 128) + (f32 ? 0.7 : 0.9);
   double least = 0.;
-  for (int sp = 1; sp < 2 * tiles; sp *= 2) {
-    const int tps = cdiv(tiles, sp), n = cdiv(tiles, tps);
-    if (tps > ROUTE_DTL_MAX_TPS || (n > 1 && blocks > ROUTE_COUNTERS)) continue;
+  for (int sp = first; sp < 2 * tiles; sp *= 2) {
+    const int tps = cdiv(tiles, sp), n = route_ranges(tiles, sp);
+    if (n > 1 && blocks > ROUTE_COUNTERS) continue;
+    if (sp > first && blocks * n > ROUTE_SPLIT_UNITS) continue;
     const double t = (double)cdiv(blocks * n, 256) *
                      (tps * tile + (f32 ? 2.5 : 2.) + (n > 1 ? 3.5 : 0.));
     if (best.splits == 0 || t < least) {
@@ -960,6 +972,25 @@ RoutePlan route_plan(int dt, int64_t rows, int S, int64_t row_bytes, bool cos) {
     p.part_entries = p.splits > 1 ? tiles * p.splits * UNIT_STREAM_ROWS : 0;
   }
   return p;
+}
+
+// The largest part_entries of any plan over at most `rows` rows (plans of
+// fewer rows may split further).
+int64_t route_part_most(int64_t rows, int S, int64_t row_bytes, bool cos) {
+  if (rows <= 0 || S <= 0) return 0;
+  // ROUTE_STREAM: t tiles in cdiv(512, t) ranges, of at least 64 keys
+  const int64_t t = std::min<int64_t>((rows + UNIT_STREAM_ROWS - 1) / UNIT_STREAM_ROWS, 511);
+  const int64_t ranges = cdiv(S, 64);
+  int64_t most = ranges > 1 ? std::min(t + 511, t * ranges) * UNIT_STREAM_ROWS : 0;
+  if (!cos && rows >= ROUTE_DTL_MIN_ROWS && row_bytes % 128 == 0) {
+    const int tiles = cdiv(S, ROUTE_DTL_KEYS);
+    const int64_t first = route_ranges(tiles, route_first_split(tiles));
+    const int64_t blocks = (rows + ROUTE_DTL_ROWS - 1) / ROUTE_DTL_ROWS;
+    const int64_t split = tiles > 1 ? std::min<int64_t>(blocks * tiles, ROUTE_SPLIT_UNITS) : 0;
+    const int64_t whole = first > 1 ? std::min<int64_t>(blocks, ROUTE_COUNTERS) * first : 0;
+    most = std::max(most, std::max(split, whole) * ROUTE_DTL_ROWS);
+  }
+  return most;
 }
 
 hipError_t launch_route(int dt, const void* q, const void* scene_keys, const float* bias,

@@ -1,6 +1,6 @@
 """The rules that choose a kernel by size, called in the built library (they
 are host code; no GPU is used): routing in the scoring kernel's shared mode or
-in the tile kernel."""
+in the tile kernel, and the partials that its splits need."""
 
 import ctypes
 
@@ -10,6 +10,7 @@ from paper_2607_16305_amd import lookme as lk
 
 F32, BF16 = 0, 1
 STREAM, SHARED, DTL = 0, 1, 2
+FAKE = 0x7F0000100000          # 256-byte aligned stand-in address, never dereferenced
 
 
 class RoutePlan(ctypes.Structure):
@@ -44,3 +45,53 @@ def test_routing_mode(dt, rows, S, row_bytes, mode):
     assert route_plan(dt, rows, S, row_bytes).mode == mode
     assert route_plan(dt, rows, S, row_bytes, True).mode != DTL
 
+
+@pytest.mark.parametrize("dt", [F32, BF16])
+@pytest.mark.parametrize("S", [1, 300, 1024, 4096, 8448, 16384])
+def test_routing_plans_fit_their_limits(dt, S):
+    """Every key tile is in one range, a range holds at most 16 tiles, split
+    blocks have a counter each, and but for the first split that holds the
+    bias table a plan makes at most 2048 units."""
+    tiles = -(-S // 256)
+    first = 1
+    while -(-tiles // first) > 16:
+        first *= 2
+    for rows in list(range(4096, 70000, 1111)) + list(range(70000, 1200000, 31013)):
+        for rb in (128, 512, 2048):
+            p = route_plan(dt, rows, S, rb)
+            if p.mode != DTL:
+                continue
+            blocks = -(-rows // 128)
+            assert p.per_split <= 16 and (p.splits - 1) * p.per_split < tiles
+            assert p.splits * p.per_split >= tiles
+            assert p.part_entries == (blocks * p.splits * 128 if p.splits > 1 else 0)
+            if p.splits > 1:
+                assert blocks <= 4096
+                assert p.splits <= first or blocks * p.splits <= 2048, (rows, rb)
+
+
+@pytest.mark.parametrize("dt", [F32, BF16])
+@pytest.mark.parametrize("S", [16, 300, 1024, 4096, 8448, 16384])
+@pytest.mark.parametrize("key_bytes", [64, 256, 1024])
+@pytest.mark.parametrize("score", [lk.LOOKME_SCORE_DOT, lk.LOOKME_SCORE_COS])
+def test_a_workspace_serves_every_smaller_batch(dt, S, key_bytes, score):
+    """lookme_workspace_size never falls with the batch, and holds what the
+    plan of the batch itself writes."""
+    desc = lk.lookme_desc_t(S, 8, key_bytes // (4 if dt == F32 else 2), 64, 4, dt, score)
+    h = lk.lookme_create(desc, FAKE, FAKE, FAKE)
+    try:
+        last = 0
+        for n in list(range(1, 300, 7)) + list(range(300, 20000, 97)) + \
+                list(range(20000, 800000, 640)):
+            size = lk.lookme_workspace_size(h, 1, n)
+            assert size >= last, n
+            last = size
+            p = route_plan(dt, n, S, key_bytes, score == lk.LOOKME_SCORE_COS)
+            assert p.part_entries * 8 < size, n
+        for layers, n in ((4, 12288), (4, 12416), (3, 16555), (2, 24801)):
+            assert lk.lookme_workspace_size(h, layers, n) <= \
+                lk.lookme_workspace_size(h, layers, n + 1000)
+            assert lk.lookme_workspace_size(h, layers - 1, n) <= \
+                lk.lookme_workspace_size(h, layers, n)
+    finally:
+        lk.lookme_destroy(h)
