@@ -128,10 +128,8 @@ Layout layout(const lookme_desc_t& d, int32_t layers, int64_t n, int32_t relevan
   const size_t es = (size_t)elem_size(d.dtype);
   L.fus_r = take(fusion_dff > 0 ? (size_t)rows * d.value_dim * es : 0);
   L.fus_u = take(fusion_dff > 0 ? (size_t)rows * fusion_dff * es : 0);
-  // the multi-scale router's queries [rows, d_v]; the size of a workspace stays
-  // what it was with the retrieved rows [scales, rows, d_v] beside them
+  // the multi-scale router's queries [rows, d_v]
   L.ms_q = take(scales > 0 ? (size_t)rows * d.value_dim * es : 0);
-  take(scales > 0 ? (size_t)scales * rows * d.value_dim * es : 0);
   L.total = off;
   return L;
 }

@@ -297,7 +297,13 @@ def test_multiscale_entry_points_validate(lib):
         assert S(lambda: lk.lookme_set_multiscale(h, 2, 2048, None)) == lk.LOOKME_ERR_INVALID
         base = lk.lookme_workspace_size(h, 1, 100)
         assert S(lambda: lk.lookme_set_multiscale(h, 2, 2048, FAKE)) == lk.LOOKME_OK
-        assert lk.lookme_workspace_size(h, 1, 100) >= base + 3 * 100 * 2048 * 2
+        # the router's queries; the retrieved rows stay in LDS
+        queries = 100 * 2048 * 2
+        assert base + queries <= lk.lookme_workspace_size(h, 1, 100) < base + 2 * queries
+        assert S(lambda: lk.lookme_set_multiscale(h, 16, 2048, FAKE)) == lk.LOOKME_ERR_UNSUPPORTED
+        assert S(lambda: lk.lookme_set_multiscale(h, 8, 2048, FAKE)) == lk.LOOKME_OK
+        assert lk.lookme_workspace_size(h, 1, 100) < base + 2 * queries
+        assert S(lambda: lk.lookme_set_multiscale(h, 2, 2048, FAKE)) == lk.LOOKME_OK
         assert S(lambda: call(d_h=4096)) == lk.LOOKME_ERR_INVALID
         assert S(lambda: call(n_keep=9)) == lk.LOOKME_ERR_INVALID
         assert S(lambda: call(n_keep=0, p=None)) == lk.LOOKME_OK
