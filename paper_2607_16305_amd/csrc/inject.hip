@@ -160,18 +160,18 @@ __global__ __launch_bounds__(INJ_THREADS) void inject_kernel(
 // twice they were 210 MB on 11520 rows of two scales, and the two launches
 // took 91 + 38.5 us (the whole gated injection 237 -> 207 us).  Bound by the
 // gather's traffic behind the caches, like the injection above; on few rows
-// by its chain of dependent loads (kept row, scene, picks, values), so below
-// MS_MANY_ROWS rows the scales of a row go to thread groups of their own,
-// side by side (500 float32 rows of four scales, the whole injection 44.7 ->
-// 35.5 us against one after another); with many rows the chip is full of them
-// and narrow workgroups run better (3000 rows of four scales 104 -> 86 us,
-// 23040 of two 235 -> 207).  Rows whose R^m do not fit the LDS (LDS = false)
-// gather twice instead.
+// by its chain of dependent loads (kept row, scene, picks, values), so the
+// scales of a row then go to thread groups of their own, side by side (50 bf16
+// rows of four scales x 2048 24.1 -> 18.9 us), while that leaves the chip room
+// for every workgroup; after that narrow workgroups run better (1500 such rows
+// 71.2 us on four groups, 67.0 on one, 11520 408 and 372), down to two groups
+// where the R^m of a row leave LDS for few workgroups a CU (8 scales x 3584:
+// 11520 rows 1091 us on one group, 952 on two).  launch_multiscale has the rows
+// that gather first (ms_gathers).
 constexpr int MS_GROUP = 256;              // threads of a scale at most
-constexpr int64_t MS_MANY_ROWS = 2048;
-constexpr int MS_LDS_BYTES = 60 * 1024;    // R^m of a row
-// threads of a row at most (k > 16 holds more loads in registers)
-constexpr int ms_threads(int k) { return k > 16 ? 512 : 1024; }
+constexpr int64_t MS_WIDE = 262144, MS_NARROW = 393216;   // threads of a launch
+constexpr int64_t MS_CU_LDS = 160 * 1024, MS_CU_THREADS = 1280;
+constexpr int MS_ROW_THREADS = 1024;       // threads of a row at most
 
 template <int DT, int K>
 __device__ __forceinline__ u32x4_t weighted_chunk(const char* __restrict__ values,
@@ -223,15 +223,15 @@ __device__ __forceinline__ float chunk_dot(u32x4_t a, u32x4_t b, float acc) {
 // groups x gs threads: group y takes scales y, y + groups, ...  A row whose
 // token id is out of range is left alone and counted once a scale; a scale
 // whose scene or a primitive is out of range has R^m = 0 and is counted.
-template <int DT, int K, bool LDS>
-__global__ __launch_bounds__(ms_threads(K)) void ms_mix_kernel(
+template <int DT, int K>
+__global__ __launch_bounds__(MS_ROW_THREADS) void ms_mix_kernel(
     int64_t n, const int32_t* __restrict__ kept, const int32_t* __restrict__ scene_all,
     const int32_t* __restrict__ prim_all, const float* __restrict__ w_all,
     const char* __restrict__ values, int Sm, int P, int k, int M, int64_t v_bytes,
     const char* __restrict__ q, char* __restrict__ hidden, int64_t h_bytes, float inv_sqrt_d,
     const int32_t* __restrict__ count, int gs) {
   __shared__ float red[MS_MAX_SCALES][MS_GROUP / WAVE];
-  extern __shared__ __attribute__((aligned(16))) char rows_lds[];   // [M, v_bytes] (LDS)
+  extern __shared__ __attribute__((aligned(16))) char rows_lds[];   // [M, v_bytes]
   const int64_t j = blockIdx.x;
   if (count != nullptr && j >= *count) return;   // past a counted list's end
   const int tid = threadIdx.x, lane = tid & 63;
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(ms_threads(K)) void ms_mix_kernel(
         r = weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c);
         dot = chunk_dot<DT>(ld16(qrow + (int64_t)c * 16), r, dot);
       }
-      if constexpr (LDS) *reinterpret_cast<u32x4_t*>(rows_lds + m * v_bytes + c * 16) = r;
+      *reinterpret_cast<u32x4_t*>(rows_lds + m * v_bytes + c * 16) = r;
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) dot += __shfl_xor(dot, d, 64);
@@ -318,15 +318,7 @@ __global__ __launch_bounds__(ms_threads(K)) void ms_mix_kernel(
 #pragma unroll
     for (int m = 0; m < MS_MAX_SCALES; ++m) {
       if (m < M) {
-        u32x4_t rv;
-        if constexpr (LDS) {
-          rv = *reinterpret_cast<const u32x4_t*>(rows_lds + m * v_bytes + c * 16);
-        } else {
-          int64_t vrow[K];
-          float wt[K];
-          rv = picks(m, vrow, wt) ? weighted_chunk<DT, K>(values, vrow, wt, k, v_bytes, c)
-                                  : u32x4_t{0, 0, 0, 0};
-        }
+        const u32x4_t rv = *reinterpret_cast<const u32x4_t*>(rows_lds + m * v_bytes + c * 16);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           if constexpr (DT == DT_BF16) {
@@ -356,31 +348,24 @@ hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const in
   const int64_t es = dt == DT_BF16 ? 2 : 4, vb = (int64_t)d_v * es;
   const int ch = (int)(vb / 16);
   const int gs = ch >= MS_GROUP ? MS_GROUP : (ch + 63) / 64 * 64;
-  const int most = n_keep < MS_MANY_ROWS ? ms_threads(k) / gs : 1;
-  const int groups = scales < most ? scales : most;
+  const int64_t room = (gs < MS_GROUP ? MS_NARROW : MS_WIDE) / (n_keep * gs);
+  const int64_t fill = MS_CU_LDS / (scales * vb + 256) * gs < MS_CU_THREADS ? 2 : 1;
+  int64_t groups = room > fill ? room : fill;
+  if (groups > scales) groups = scales;
+  if (groups > MS_ROW_THREADS / gs) groups = MS_ROW_THREADS / gs;
+  const int64_t turns = (scales + groups - 1) / groups;
+  groups = (scales + turns - 1) / turns;   // as even as the turns allow
   const float inv_sqrt_d = 1.0f / sqrtf((float)d_v);
-  const bool lds = scales * vb <= MS_LDS_BYTES;
-#define LOOKME_MS(DT_, K_, L_)                                                                  \
-  hipLaunchKernelGGL((ms_mix_kernel<DT_, K_, L_>), dim3((unsigned)n_keep), dim3(gs * groups),   \
-                     L_ ? (unsigned)(scales * vb) : 0u, st, n, kept, scene, prim, w,            \
-                     static_cast<const char*>(values), Sm, P, k, scales, vb,                    \
-                     static_cast<const char*>(q), static_cast<char*>(hidden), d_h * es,         \
-                     inv_sqrt_d, count, gs)
-#define LOOKME_MS_K(DT_, L_)                  \
-  do {                                        \
-    if (k <= 8) LOOKME_MS(DT_, 8, L_);        \
-    else if (k <= 16) LOOKME_MS(DT_, 16, L_); \
-    else LOOKME_MS(DT_, 32, L_);              \
-  } while (0)
-  if (dt == DT_BF16) {
-    if (lds) LOOKME_MS_K(DT_BF16, true);
-    else LOOKME_MS_K(DT_BF16, false);
-  } else {
-    if (lds) LOOKME_MS_K(DT_F32, true);
-    else LOOKME_MS_K(DT_F32, false);
-  }
-#undef LOOKME_MS_K
-#undef LOOKME_MS
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_keep), dim3((unsigned)(gs * groups)),
+                       (unsigned)(scales * vb), st, n, kept, scene, prim, w,
+                       static_cast<const char*>(values), Sm, P, k, scales, vb,
+                       static_cast<const char*>(q), static_cast<char*>(hidden), d_h * es,
+                       inv_sqrt_d, count, gs);
+  };
+  if (dt != DT_BF16) launch(ms_mix_kernel<DT_F32, 8>);
+  else if (k <= 8) launch(ms_mix_kernel<DT_BF16, 8>);
+  else launch(ms_mix_kernel<DT_BF16, 16>);
   return hipGetLastError();
 }
 

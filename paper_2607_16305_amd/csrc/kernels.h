@@ -191,8 +191,21 @@ hipError_t launch_propagate(int dt, const void* w_p_t, int steps, int64_t n_keep
 // and w [M, n, k]) gives R^m of every kept token; q = round(H[kept] W_he) into
 // q [n_keep, d_v] (w_he_t [d_v, d_h], output-row-major); then H[t, :d_v] =
 // round(H + sum_m alpha_m R^m) with alpha = softmax_m(q . R^m / sqrt(d_v))
-// (launch_ms_mix).
+// (launch_ms_mix, or by way of r).
 constexpr int MS_MAX_SCALES = 8;
+constexpr int MS_LDS_BYTES = 60 * 1024;   // the R^m of a row that the mix keeps in LDS
+// Whether the rows R^m are gathered into r [M, n_keep, d_v] by a launch of
+// their own and mixed by a second one, instead of both in one.  One launch
+// saves R's way through memory, and wins wherever its k value rows in
+// registers and the R^m in LDS leave enough waves a CU: up to 8 picks always
+// (bf16 8 x 3584: 11520 rows 1013 -> 952 us, 2 x 512: 56.1 -> 49.3), up to 16
+// in bf16 on few rows of few scales (4 x 2048: 1500 rows 86.3 -> 83.7, 11520
+// 473 -> 496; 8 x 2048 1500 rows 137 -> 141; float32 2 x 1024 77.1 -> 91.8),
+// with more not (4 x 2048, k = 32: 1500 rows 141 -> 173).
+inline bool ms_gathers(bool f32, int scales, int64_t row_bytes, int k, int64_t rows) {
+  if (scales * row_bytes > MS_LDS_BYTES) return true;
+  return k > 8 && (f32 || k > 16 || scales > 4 || rows >= 4096);
+}
 hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const int32_t* kept,
                          const int32_t* scene, const int32_t* prim, const float* w,
                          const void* values, int Sm, int P, int d_v, int k, const void* q,
@@ -200,7 +213,7 @@ hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const in
 hipError_t launch_multiscale(int dt, int scales, int64_t n, int64_t n_keep, const int32_t* kept,
                              const int32_t* scene, const int32_t* prim, const float* w,
                              const void* values, int S, int P, int d_v, int k,
-                             const void* w_he_t, int d_h, void* hidden, void* q,
+                             const void* w_he_t, int d_h, void* hidden, void* r, void* q,
                              hipStream_t st, const int32_t* count = nullptr);
 
 // ---- Level-2 scoring of bucketed rows, fused top-k + softmax --------------

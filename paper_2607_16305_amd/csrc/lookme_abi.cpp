@@ -78,7 +78,7 @@ constexpr int32_t MAX_SCENES = 16384;   // bucketing keeps one histogram per chu
 struct Layout {
   size_t chunk_hist, local_rank, offsets, perm, unit_scene, unit_begin, unit_count, route_count,
       route_part, split_row, split_part, crit_key, kept, rel_tab, rel_logits, fus_r, fus_u, ms_q,
-      total;
+      ms_r, total;
 };
 
 // The leading bytes of the workspace hold counters that start at zero; they
@@ -128,8 +128,12 @@ Layout layout(const lookme_desc_t& d, int32_t layers, int64_t n, int32_t relevan
   const size_t es = (size_t)elem_size(d.dtype);
   L.fus_r = take(fusion_dff > 0 ? (size_t)rows * d.value_dim * es : 0);
   L.fus_u = take(fusion_dff > 0 ? (size_t)rows * fusion_dff * es : 0);
-  // the multi-scale router's queries [rows, d_v]
+  // the multi-scale router's queries [rows, d_v] and, where they are gathered
+  // first, the retrieved rows [scales, rows, d_v]
   L.ms_q = take(scales > 0 ? (size_t)rows * d.value_dim * es : 0);
+  L.ms_r = take(scales > 0 && lookme::ms_gathers(d.dtype == LOOKME_F32, scales,
+                                                 d.value_dim * (int64_t)es, d.top_k, rows)
+                    ? (size_t)scales * rows * d.value_dim * es : 0);
   L.total = off;
   return L;
 }
@@ -1118,7 +1122,7 @@ lookme_status_t lookme_inject_multiscale(lookme_t h, int64_t n, int64_t n_keep,
   return hip_status(lookme::launch_multiscale(d.dtype, h->ms_scales, n, n_keep, kept, scene,
                                               prim, w, h->values, d.num_scenes,
                                               d.prims_per_scene, d.value_dim, d.top_k, h->ms_w,
-                                              d_h, hidden, ws + L.ms_q, st),
+                                              d_h, hidden, ws + L.ms_r, ws + L.ms_q, st),
                     "multi-scale injection launch");
 }
 
@@ -1144,7 +1148,7 @@ lookme_status_t lookme_inject_multiscale_gated(lookme_t h, int64_t n, const int3
   return hip_status(lookme::launch_multiscale(d.dtype, h->ms_scales, n, n, kept, scene, prim, w,
                                               h->values, d.num_scenes, d.prims_per_scene,
                                               d.value_dim, d.top_k, h->ms_w, d_h, hidden,
-                                              ws + L.ms_q, st, count),
+                                              ws + L.ms_r, ws + L.ms_q, st, count),
                     "multi-scale injection launch");
 }
 

@@ -297,13 +297,21 @@ def test_multiscale_entry_points_validate(lib):
         assert S(lambda: lk.lookme_set_multiscale(h, 2, 2048, None)) == lk.LOOKME_ERR_INVALID
         base = lk.lookme_workspace_size(h, 1, 100)
         assert S(lambda: lk.lookme_set_multiscale(h, 2, 2048, FAKE)) == lk.LOOKME_OK
-        # the router's queries; the retrieved rows stay in LDS
+        # the router's queries; the retrieved rows stay in LDS at this width and k
         queries = 100 * 2048 * 2
         assert base + queries <= lk.lookme_workspace_size(h, 1, 100) < base + 2 * queries
         assert S(lambda: lk.lookme_set_multiscale(h, 16, 2048, FAKE)) == lk.LOOKME_ERR_UNSUPPORTED
         assert S(lambda: lk.lookme_set_multiscale(h, 8, 2048, FAKE)) == lk.LOOKME_OK
         assert lk.lookme_workspace_size(h, 1, 100) < base + 2 * queries
         assert S(lambda: lk.lookme_set_multiscale(h, 2, 2048, FAKE)) == lk.LOOKME_OK
+        wide = lk.lookme_create(_desc(dtype=lk.LOOKME_BF16, key_dim=512, value_dim=2048,
+                                      prims_per_scene=1024, top_k=32, num_scenes=256), FAKE,
+                                FAKE, FAKE)
+        try:   # 32 picks: the rows are gathered into the workspace first
+            assert S(lambda: lk.lookme_set_multiscale(wide, 2, 2048, FAKE)) == lk.LOOKME_OK
+            assert lk.lookme_workspace_size(wide, 1, 100) >= base + 3 * queries
+        finally:
+            lk.lookme_destroy(wide)
         assert S(lambda: call(d_h=4096)) == lk.LOOKME_ERR_INVALID
         assert S(lambda: call(n_keep=9)) == lk.LOOKME_ERR_INVALID
         assert S(lambda: call(n_keep=0, p=None)) == lk.LOOKME_OK
