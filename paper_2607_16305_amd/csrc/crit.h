@@ -198,18 +198,21 @@ constexpr int sel_cache_words(int cn) { return cn > 0 ? cn : 1; }
 // of its LDS reads (32768 keys: 32 a thread), so: 32-bit indices, a wave's
 // keys read side by side, bins in eight copies (a lane adds to copy lane mod
 // 8: keys of one batch share few leading digits, and adds to one LDS word go
-// one after the other), and once two digits are known the few keys that
-// share them are ranked directly instead of by two more passes over all keys.
-// 32768 keys 41 -> 28 us, 4 x 23040 32 -> 19.
+// one after the other), and once the keys that share the digits found so far
+// are few they are ranked directly instead of by more passes over all keys.
+// 32768 keys 41 -> 28 us, 4 x 23040 32 -> 19.  Few: the ranking compares each
+// with each, 256 take about one of the passes it saves (norms within 6% of one
+// another: with up to 1024 ranked 23040 keys took 49.4 us, with 256 26.1;
+// 16384 33.8 and 21.1).
 template <int CN, int THREADS = SEL_THREADS>
 __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, int64_t n64,
                                              int64_t n_keep64, int32_t* __restrict__ kept,
                                              uint32_t* cache, SelLds& sl) {
   constexpr bool CACHED = CN > 0;
   constexpr int WAVES = THREADS / WAVE, BATCH = 8;
-  constexpr int LIST = 1024;   // keys ranked directly, in the bins' words
+  constexpr int LIST = 256;   // keys ranked directly, in the bins' words
   static_assert(THREADS % 256 == 0, "a thread per radix bin");
-  static_assert(WAVES <= SEL_WAVES && LIST <= 256 * SEL_COPIES, "scan partials, list");
+  static_assert(WAVES <= SEL_WAVES && LIST <= THREADS, "scan partials, a thread per listed key");
   int* hist = sl.hist;
   int* wsum = sl.wsum;
   if (n_keep64 == 0) return;
@@ -278,25 +281,27 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
     need = sl.need;
     mask |= 255u << shift;
     const int left = sl.total;   // keys that share the digits found so far
-    if (pass == 1 && left <= LIST) {
-      // every one of them into a list, then each key's rank in it
+    if (pass >= 1 && pass < 3 && left <= LIST) {
+      // every one of them into a list; the one sought is the smallest with
+      // fewer than `need` above it
       each([&](int, uint32_t k) {
-        if ((k & mask) == prefix) hist[atomicAdd(&sl.listed, 1)] = (int)k;
+        if ((k & mask) == prefix) {
+          const int at = atomicAdd(&sl.listed, 1);
+          if (at < LIST) hist[at] = (int)k;
+        }
       });
+      if (tid == 0) sl.prefix = 0xFFFFFFFFu;
       __syncthreads();
-      for (int t = tid; t < left; t += THREADS) {
-        const uint32_t x = (uint32_t)hist[t];
-        int gt = 0, ge = 0;
-        for (int j = 0; j < left; ++j) {
-          const uint32_t y = (uint32_t)hist[j];
-          gt += y > x;
-          ge += y >= x;
-        }
-        if (gt < need && need <= ge) {   // equal keys store equal values
-          sl.prefix = x;
-          sl.total = need - gt;
-        }
+      uint32_t x = 0;
+      int gt = 0;
+      if (tid < left) {
+        x = (uint32_t)hist[tid];
+#pragma unroll 8
+        for (int j = 0; j < left; ++j) gt += (uint32_t)hist[j] > x;
+        if (gt < need) atomicMin(&sl.prefix, x);
       }
+      __syncthreads();
+      if (tid < left && x == sl.prefix) sl.total = need - gt;   // equal keys: equal values
       __syncthreads();
       prefix = sl.prefix;
       need = sl.total;

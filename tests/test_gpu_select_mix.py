@@ -1,8 +1,10 @@
 """The top-n_keep select, the gate compaction and the multi-scale mix at the
 sizes where their splits can go wrong, against plain definitions: one wave's
-groups and ragged ones, the LDS caches' limits and the uncached form, all keys
+groups and ragged ones, the LDS caches' limits and the uncached forms (through
+lookme_select, which may run beside other kernels, and lookme_inject), all keys
 equal (more than the direct ranking holds), keys that share their leading
-digits, and rows of one, two and more chunks a thread."""
+digits, as many of them as the ranking holds and one more, and rows of one, two
+and more chunks a thread."""
 
 import numpy as np
 import pytest
@@ -22,11 +24,39 @@ def _table():
     return lk.Table(inp["scene_keys"], inp["prim_keys"], inp["values"], 2)
 
 
+def _injected(tab, crit, keep):
+    """The kept set that lookme_inject writes (its own form of the select)."""
+    layers, n = crit.shape[:2]
+    kept = torch.full((layers, keep), -7, dtype=torch.int32, device=DEV)
+    scene = torch.zeros((layers, n), dtype=torch.int32, device=DEV)
+    prim = torch.zeros((layers, n, 2), dtype=torch.int32, device=DEV)
+    w = torch.zeros((layers, n, 2), device=DEV)
+    hidden = torch.zeros((layers, n, 16), device=DEV)
+    tab.inject(crit, scene, prim, w, hidden, keep, kept, layers=layers)
+    return kept
+
+
+def _check_kept(crit, squares, keeps):
+    """kept of both forms = the n_keep largest, lowest token on ties.
+    squares [layers, n]: the exact sums of squares."""
+    tab = _table()
+    for keep in keeps:
+        kept = torch.full((crit.shape[0], keep), -7, dtype=torch.int32, device=DEV)
+        tab.select(crit, kept, keep, layers=crit.shape[0])
+        other = _injected(tab, crit, keep)
+        torch.cuda.synchronize()
+        for l, sq in enumerate(squares):
+            want = np.sort(np.argsort(-sq, kind="stable")[:keep])
+            assert np.array_equal(kept[l].cpu().numpy(), want), (keep, l)
+            assert np.array_equal(other[l].cpu().numpy(), want), ("inject", keep, l)
+
+
 @pytest.mark.parametrize("values", ["spread", "equal", "near", "few"])
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000, 1025, 4096, 4097, 32768, 32769, 70001])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000, 1025, 4096, 4097, 8192, 8193, 32767, 32768,
+                               32769, 70001])
 def test_select_is_the_stable_top(n, values):
     """One nonzero element a row, a small integer or power of two, so that
-    every square is exact: kept = the n_keep largest, lowest token on ties."""
+    every square is exact."""
     print(f"[select-mix] select n {n} {values}", flush=True)
     rng = np.random.default_rng(n)
     x = {"spread": np.exp2(rng.integers(-20, 20, n)) * rng.integers(1, 100, n),
@@ -35,13 +65,44 @@ def test_select_is_the_stable_top(n, values):
     crit = torch.zeros((2, n, 4), device=DEV)
     crit[0, :, 1] = torch.tensor(x, device=DEV, dtype=torch.float32)
     crit[1, :, 2] = torch.tensor(x[::-1].copy(), device=DEV, dtype=torch.float32)
-    tab = _table()
-    for keep in sorted({1, max(1, n // 3), n}):
-        kept = torch.full((2, keep), -7, dtype=torch.int32, device=DEV)
-        tab.select(crit, kept, keep, layers=2)
+    _check_kept(crit, [(v.astype(np.float32) ** 2).astype(np.float32) for v in (x, x[::-1])],
+                sorted({1, max(1, n // 3), n}))
+
+
+@pytest.mark.parametrize("n,layers,width", [(5000, 2, 64), (9000, 2, 64), (40000, 2, 64),
+                                            (9000, 4, 1024)])
+@pytest.mark.parametrize("listed", [1, 255, 256, 257, 700])
+def test_select_among_keys_that_share_their_digits(n, layers, width, listed):
+    """`listed` keys 1 + m^2 2^-22 with m < 180 share their 16 leading bits;
+    the boundary falls among them, the others are well below and above.  Many
+    layers of wide keys (a projection of several rounds) run lookme_select in
+    lookme_inject's form."""
+    print(f"[select-mix] listed {listed} of {n}, {layers} layers", flush=True)
+    rng = np.random.default_rng(n + listed)
+    m = rng.integers(0, 180, (layers, n))
+    at = np.argsort(rng.random((layers, n)), axis=1)
+    big = n // 4
+    one, two = np.ones((layers, n)), m * 2.0 ** -11
+    for l in range(layers):
+        one[l, at[l, listed:listed + big]], two[l, at[l, listed:listed + big]] = 2.0, 0.0
+        one[l, at[l, listed + big:]], two[l, at[l, listed + big:]] = 0.5, 0.0
+    crit = torch.zeros((layers, n, 4), device=DEV)
+    crit[:, :, 0] = torch.tensor(one, device=DEV)
+    crit[:, :, 3] = torch.tensor(two, device=DEV)
+    squares = [(a * a + b * b).astype(np.float32) for a, b in zip(one, two)]
+    keeps = sorted({big + 1, big + listed // 2 + 1, big + listed})
+    if width == 64:
+        return _check_kept(crit, squares, keeps)
+    from paper_2607_16305_amd import lookme as lk
+    zeros = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device=DEV)
+    tab = lk.Table(zeros(2, width), zeros(2, 4, width), zeros(8, 16), 2)
+    wide = crit.to(torch.bfloat16)   # m 2^-11 and the others are bf16 values
+    wide = torch.cat([wide, torch.zeros_like(wide)], 2)
+    for keep in keeps:
+        kept = torch.full((layers, keep), -7, dtype=torch.int32, device=DEV)
+        tab.select(wide, kept, keep, layers=layers)
         torch.cuda.synchronize()
-        for l, v in enumerate((x, x[::-1])):
-            sq = (v.astype(np.float32) ** 2).astype(np.float32)
+        for l, sq in enumerate(squares):
             want = np.sort(np.argsort(-sq, kind="stable")[:keep])
             assert np.array_equal(kept[l].cpu().numpy(), want), (keep, l)
 
