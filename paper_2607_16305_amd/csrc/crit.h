@@ -338,12 +338,10 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
   e = __builtin_amdgcn_readfirstlane(e);
   each([&](int i, uint32_t k) {
     const uint64_t mg = __ballot(k > T), me = __ballot(k == T);
-    if (k > T) kept[g + bits_below(mg) + min(e + bits_below(me), take_eq)] = i;
-    if (me != 0) {
-      const int eb = e + bits_below(me);
-      if (k == T && eb < take_eq) kept[g + bits_below(mg) + eb] = i;
-      e += __popcll(me);
-    }
+    const int eb = e + bits_below(me);
+    const int at = g + bits_below(mg) + min(eb, take_eq);
+    if ((k > T || (k == T && eb < take_eq)) && at < n_keep) kept[at] = i;
+    e += __popcll(me);
     g += __popcll(mg);
   });
 }
