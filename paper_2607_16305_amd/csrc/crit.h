@@ -28,9 +28,9 @@ constexpr int SEL_WAVES = SEL_THREADS / WAVE;
 // CN > 0: a layer's keys (n <= CN) are first copied to LDS, so that the four
 // passes and the compaction read them there instead of from L2 (one global
 // round trip instead of five).  Launchers take the smallest cache that holds
-// n: the small one leaves room on the CU for the workgroups of a kernel that
+// n: the smaller ones leave room on the CU for the workgroups of a kernel that
 // runs beside the select.
-constexpr int SEL_CACHE_SMALL = 4096, SEL_CACHE_N = 32768;
+constexpr int SEL_CACHE_SMALL = 4096, SEL_CACHE_MID = 8192, SEL_CACHE_N = 32768;
 
 template <int DT>
 __device__ __forceinline__ float row_sumsq(const char* __restrict__ p, int chunks, int lane) {

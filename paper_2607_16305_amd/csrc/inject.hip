@@ -416,12 +416,18 @@ hipError_t launch_crit_select(int layers, int64_t n, int64_t n_keep, const uint3
   // beside the projection and routing of a second stream the large cache's
   // 132 KiB (and 16 waves) find no CU before those have ended, and the select
   // then runs into Level-2's start: 8 waves reading the keys from L2 fit
-  // beside them (step of 32768 tokens 2.23 -> 2.17 ms)
-  if (background && n > SEL_CACHE_SMALL)
+  // beside them (32768 tokens: select 122 -> 69 us beside the step's other
+  // kernels, alone 32.9 us cached and 37.7 so).  Up to SEL_CACHE_MID keys the
+  // cache leaves the room as well (4097 keys 20.7 -> 14.5 us alone, 8192 28.5
+  // -> 15.4)
+  if (background && n > SEL_CACHE_MID)
     hipLaunchKernelGGL((crit_select_kernel<0, SEL_THREADS / 2>), dim3(layers),
                        dim3(SEL_THREADS / 2), 0, st, key, n, n_keep, kept);
   else if (n <= SEL_CACHE_SMALL)
     hipLaunchKernelGGL(crit_select_kernel<SEL_CACHE_SMALL>, dim3(layers), dim3(SEL_THREADS), 0, st,
+                       key, n, n_keep, kept);
+  else if (n <= SEL_CACHE_MID)
+    hipLaunchKernelGGL(crit_select_kernel<SEL_CACHE_MID>, dim3(layers), dim3(SEL_THREADS), 0, st,
                        key, n, n_keep, kept);
   else if (n <= SEL_CACHE_N)
     hipLaunchKernelGGL(crit_select_kernel<SEL_CACHE_N>, dim3(layers), dim3(SEL_THREADS), 0, st,
