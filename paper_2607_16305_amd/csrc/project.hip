@@ -4,12 +4,12 @@
 //
 // C[M, N] = A[M, K] . B[N, K]^T with A = x [n, d_in], B = W^T stacked
 // [layers * d_e, d_in]; C is rounded once to the storage dtype and scattered
-// to q[layer, token, :].  Large batches run as a tile_gemm.h
-// product.  The others are tiled on LDS here: a BM x BN
-// output tile per 4 waves in a 2 x 2 grid, 128-byte K stages double-buffered
-// in LDS (rows padded by 16 bytes so the 16-byte fragment reads of 8
-// consecutive rows hit distinct banks), the global loads of the next D stages
-// in flight while one is multiplied.
+// to q[layer, token, :].  Large batches run as a tile_gemm.h product, or on
+// project_round_kernel where they are one round of 256 x 256 tiles.  The
+// others are tiled on LDS here: a BM x BN output tile per 4 waves in a 2 x 2
+// grid, 128-byte K stages double-buffered in LDS (rows padded by 16 bytes so
+// the 16-byte fragment reads of 8 consecutive rows hit distinct banks), the
+// global loads of the next D stages in flight while one is multiplied.
 #include "common.h"
 #include "kernels.h"
 #include "tile_gemm.h"
@@ -205,6 +205,106 @@ __global__ __launch_bounds__(PJ_THREADS * KG) void project_kernel(
   store_tile<DT, MI, NJ>(acc, Q, M, N, d_e, m0 + wm, n0 + wn, n16, g);
 }
 
+// One round of 256 x 256 tiles (at most one a CU), fed by direct global-to-LDS
+// loads: 16 waves in 4 x 4, each 4 x 4 MFMA tiles, two 128-byte K stages (the
+// loads of stage s + 1 fly during stage s).  Its waves take a quarter of a
+// SIMD's registers less than the phased kernel's (tile_gemm.h) and so leave
+// room for a wave of another stream's norms or select, which the phased
+// kernel does not; see launch_project.  A load instruction fills 1 KB:
+// neighbouring lanes read one row's contiguous bytes, whose 16-byte chunks
+// are permuted by blk_swz so that the fragment reads hit distinct LDS banks.
+constexpr int PR_WM = 4, PR_WN = 4, PR_MI = 4, PR_NJ = 4, PR_KB = 128;
+using PrShape = DtlShape<PR_WM, PR_WN, PR_MI, PR_NJ, PR_KB>;
+
+template <int DT>
+__global__ __launch_bounds__(64 * PR_WM * PR_WN) void project_round_kernel(
+    const char* __restrict__ A, const char* __restrict__ B, char* __restrict__ Q, int64_t M,
+    int N, int64_t k_bytes, int d_e, int tiles) {
+  using S = PrShape;
+  constexpr int MI = PR_MI, NJ = PR_NJ, KB = PR_KB, KSL = KB / 64;
+  __shared__ __attribute__((aligned(1024))) char lds[2][S::STAGE];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n16 = lane & 15, g = lane >> 4;
+  const int wm = (wv / PR_WN) * 16 * MI, wn = (wv % PR_WN) * 16 * NJ;
+
+  const int tiles_n = (N + S::BN - 1) / S::BN;
+  const int tile = xcd_remap(blockIdx.x, tiles);
+  if (tile < 0) return;
+  const int64_t m0 = (int64_t)(tile / tiles_n) * S::BM;
+  const int n0 = (tile % tiles_n) * S::BN;
+  const int nst = (int)(k_bytes / KB);
+
+  // load q of a stage covers tile rows [q RPI, q RPI + RPI) (A rows first,
+  // then B rows).  Rows past the edge are clamped into the operand and feed
+  // only outputs that are never stored.
+  const char* src[S::PER_WAVE];
+#pragma unroll
+  for (int b = 0; b < S::PER_WAVE; ++b) {
+    const int trow = (wv * S::PER_WAVE + b) * S::RPI + lane / S::LPR;
+    const int chunk = (lane % S::LPR) ^ blk_swz<KB>(trow & 15);
+    if (trow < S::BM) {
+      int64_t r = m0 + trow;
+      r = r < M ? r : M - 1;
+      src[b] = A + r * k_bytes + chunk * 16;
+    } else {
+      int r = n0 + trow - S::BM;
+      r = r < N ? r : N - 1;
+      src[b] = B + (int64_t)r * k_bytes + chunk * 16;
+    }
+  }
+  auto issue = [&](int stage) {
+    const int s = stage < nst ? stage : nst - 1;   // past the end: a harmless reload
+    char* dst = lds[stage & 1];
+#pragma unroll
+    for (int b = 0; b < S::PER_WAVE; ++b)
+      load_lds16(src[b] + (int64_t)s * KB, dst + (wv * S::PER_WAVE + b) * 1024);
+  };
+
+  f32x4_t acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  issue(0);
+  for (int s = 0; s < nst; ++s) {
+    // stage s has landed everywhere and every read of stage s - 1 (the other
+    // buffer) has ended (a plain s_barrier: the empty asm keeps LDS accesses
+    // on their side of it)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue(s + 1);
+    const char* buf = lds[s & 1];
+    u32x4_t fa[KSL][MI], fb[KSL][NJ];
+#pragma unroll
+    for (int ks = 0; ks < KSL; ++ks) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) fa[ks][i] = read_frag<KB>(buf, wm + 16 * i, ks, n16, g);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) fb[ks][j] = read_frag<KB>(buf, S::BM + wn + 16 * j, ks, n16, g);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KSL; ++ks)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = mfma_chunk<DT>(fa[ks][i], fb[ks][j], acc[i][j]);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into LDS outlives the wave
+  store_tile<DT, MI, NJ>(acc, Q, M, N, d_e, m0 + wm, n0 + wn, n16, g);
+}
+
+template <int DT>
+static void launch_round(const void* x, const void* wt, void* q, int64_t n, int N, int64_t kb,
+                         int d_e, int tiles, hipStream_t st) {
+  hipLaunchKernelGGL(project_round_kernel<DT>, dim3((unsigned)((tiles + 7) / 8 * 8)),
+                     dim3(64 * PR_WM * PR_WN), 0, st, static_cast<const char*>(x),
+                     static_cast<const char*>(wt), static_cast<char*>(q), n, N, kb, d_e, tiles);
+}
+
 template <int DT, int BM, int BN, int D, int KG>
 static void launch_tiles(const void* x, const void* wt, void* q, int64_t n, int N, int64_t kb,
                          int d_e, hipStream_t st) {
@@ -222,6 +322,23 @@ hipError_t launch_project(int dt, const void* x, const void* wt, void* q, int64_
   const int es = dt == DT_BF16 ? 2 : 4;
   const int N = layers * d_e;
   const int64_t kb = (int64_t)d_in * es;
+  // One nearly full round of large tiles leaves no CU to the norms and the
+  // select of a second stream, which then hold up the routing: beside them the
+  // phased kernel, whose tiles fill a CU's registers, made the step of 32768
+  // rows 2.235 ms, its 128 x 256 tiles in two rounds 2.169 (projection 150 us),
+  // project_round_kernel 2.147 (134 us).  Alone: 32768 x 512 x 4096 113 us
+  // phased, 122 here; 32768 x 512 x 2048 69.5 us on 128 x 256 tiles, 64.6 here;
+  // float32 616 us on 64 x 64 tiles, 567 here.  bf16 sums of at most 1 KiB of
+  // K are over before the phased pipeline is full, so half a round is enough
+  // for it there (5000 x 2048 x 512 26.9 us phased, 25.5 here; 16384 x 512 x
+  // 512 25.7 us on 64 x 64 tiles, 24.9 here).
+  const int64_t large = ((n + 255) / 256) * ((N + 255) / 256);
+  if (kb % PR_KB == 0 && large <= 256 &&
+      large > (dt == DT_BF16 && kb <= 1024 ? 127 : 224)) {
+    if (dt == DT_BF16) launch_round<DT_BF16>(x, wt, q, n, N, kb, d_e, (int)large, st);
+    else launch_round<DT_F32>(x, wt, q, n, N, kb, d_e, (int)large, st);
+    return hipGetLastError();
+  }
   // The 32 x 64 tiles below split K over four wave groups, one workgroup a CU:
   // right while every tile has a CU of its own (1024 x 512 x 2048, 256 tiles:
   // 10.9 us against 12.1 on 64 x 64 tiles), slow after (2000 x 512 x 2048

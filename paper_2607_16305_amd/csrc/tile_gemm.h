@@ -601,21 +601,6 @@ __global__ __launch_bounds__(512, 2) void phase_gemm_kernel(TileGemmParams a) {
   }
 }
 
-// 128 x 256 tiles, two rounds for one of 256 x 256: about 170 registers and
-// 96 KiB of LDS, so that a CU still takes workgroups of another stream (the
-// projection; see launch_tile_gemm).
-template <int DT, int EPI>
-__global__ __launch_bounds__(512, 2) void phase_gemm_open_kernel(TileGemmParams a) {
-  using S = PgShape<2, 2>;
-  static_assert(EPI != EPI_SWIGLU, "one B operand");
-  __shared__ __attribute__((aligned(1024))) char lds[2 * S::BUF];
-  const int tn = (a.cols + S::BN - 1) / S::BN;
-  const int tile = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, a.tiles));
-  if (tile < 0) return;
-  const int tm = __builtin_amdgcn_readfirstlane(tile / tn);
-  phase_tile<DT, EPI, 2, 2>(a, lds, 0, a.rows, (int64_t)tm * S::BM, (tile - tm * tn) * S::BN);
-}
-
 template <int EPI>
 static int64_t phase_tiles(const TileGemmParams& p, int batches) {
   using S = PgShape<4, 2>;
@@ -666,19 +651,6 @@ hipError_t launch_tile_gemm(int dt, TileGemmParams p, int batches, hipStream_t s
                     (p.a_sel == nullptr || p.sel_rows * p.a_bytes < ((int64_t)1 << 32));
   const int64_t large = phase_tiles<EPI>(p, batches);
   if (p.cols % 8 == 0 && near && large >= (dt != DT_BF16 ? 512 : p.k_bytes > 1024 ? 48 : 129)) {
-    if constexpr (EPI == EPI_Q) {
-      // A projection that is one nearly full round would leave no CU to the
-      // select of a second stream, which then delays the routing after it
-      // (32768 x 512 x 4096, 256 tiles, beside the select: projection and
-      // routing 118 + 233 us; alone the tiles that leave room take 125 us
-      // against 113).
-      if (dt == DT_BF16 && large > 224 && large <= PH_ROUND) {
-        p.tiles = (int)((p.rows + 127) / 128 * ((p.cols + 255) / 256));
-        hipLaunchKernelGGL((phase_gemm_open_kernel<DT_BF16, EPI>),
-                           dim3((unsigned)((p.tiles + 7) / 8 * 8)), dim3(512), 0, st, p);
-        return hipGetLastError();
-      }
-    }
     return launch_phase<EPI>(dt, p, batches, st);
   }
   if constexpr (EPI != EPI_SWIGLU) {

@@ -4,8 +4,8 @@ wins), at the sizes where the tile kernel can go wrong: fewer scenes than a
 key tile, ragged last tiles and row blocks, one and several key tiles a
 workgroup, split and unsplit ranges, one K stage and several, and on either
 side of the rule that gives many rows over few scenes to the scoring kernel;
-and projections of the middle sizes, on either side of the rule that gives
-them 64 x 64 tiles."""
+and projections of the middle sizes, on either side of the rules that give
+them 64 x 64 tiles or one round of 256 x 256 ones."""
 
 import pytest
 import torch
@@ -74,3 +74,27 @@ def test_projection_of_middle_sizes(n, layers, d_e, d_in):
     want = torch.stack([x.float() @ wt[l].float().T for l in range(layers)])
     assert torch.equal(q, want.to(dt))   # |sums| < 256: bf16 holds them exactly
 
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,layers,d_e,d_in", [
+    (7900, 3, 480, 64), (8192, 4, 512, 320),     # 186 and 256 tiles of 256 x 256
+    (7930, 4, 480, 192),                         # 248, ragged both ways, 3 (6) K stages
+    (4200, 4, 512, 512),                         # 136, K of 1 KiB: bf16 on large tiles
+])
+def test_projection_of_one_round(n, layers, d_e, d_in, dtype):
+    from paper_2607_16305_amd import lookme as lk
+    print(f"[route-tiles] projection {dtype} n {n} layers {layers} d_e {d_e} d_in {d_in}",
+          flush=True)
+    g = torch.Generator(DEV).manual_seed(n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randint(-1, 2, (n, d_in), generator=g, device=DEV).to(dt)
+    wt = torch.randint(-1, 2, (layers, d_e, d_in), generator=g, device=DEV).to(dt)
+    keys = torch.randint(-2, 3, (3, d_e), generator=g, device=DEV).to(dt)
+    tab = lk.Table(keys, torch.zeros((3, 1, d_e), dtype=dt, device=DEV),
+                   torch.zeros((3, 64), dtype=dt, device=DEV), 1)
+    q = torch.full((layers, n, d_e), 7.0, dtype=dt, device=DEV)
+    scene = torch.empty((layers, n), dtype=torch.int32, device=DEV)
+    tab.route(x, wt, q, scene, layers=layers)
+    torch.cuda.synchronize()
+    for l in range(layers):   # |sums| < 256: bf16 holds them exactly
+        assert torch.equal(q[l], (x.float() @ wt[l].float().T).to(dt)), l
