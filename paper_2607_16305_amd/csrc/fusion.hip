@@ -20,6 +20,28 @@
 
 namespace lookme {
 
+// bf16: the phased kernel from 48 tiles of 256 x 256 on (192 quarters): 2304 x
+// 2048 x 2048 for four layers 310 -> 149 us (gate/up) and 147 -> 85 us (down),
+// 512 x 2048 x 2048 for four layers (64 tiles) 31 -> 24.5 us; below it too few
+// of the CUs get one: 1024 x 2048 x 2048 (32 tiles) 17.2 us on 64 x 64 tiles,
+// 18.0 phased, 512 x 2048 x 2048 13.2 and 16.5.  Short sums (K of at most 1 KiB
+// a row) are over before the deeper pipeline pays, so they take it where most
+// of a round is whole tiles (relevance lookups of 20011 rows, 158 tiles, 131.9
+// us on 64 x 64 tiles and 129.1 phased; of 12000, 94 tiles, 125.2 and 132.2;
+// 4000 x 2048 x 512, 128, 19.0 and 20.5).
+// float32 is bound by the matrix cores on either, and 64 x 64 tiles fill a last
+// round better: a round of whole phased tiles takes as long as 205 tiles'
+// worth of them, a round of quarters 0.35 of that (projection of 256 tiles,
+// K of 8 KiB, 616 us on 64 x 64 tiles, half of 512 tiles' 966 phased; fused
+// injection of 4000 rows x 2048 x 2048, 256 and 128 tiles, 953 -> 829 us).
+bool product_phased(int dt, int64_t tiles, int64_t k_bytes) {
+  if (dt == DT_BF16) return tiles >= (k_bytes > 1024 ? 48 : 129);
+  const PhasePlan pl = phase_plan((int)tiles);
+  const double rounds = (pl.whole + PH_ROUND - 1) / PH_ROUND +
+                        0.35 * ((4 * pl.cut + PH_ROUND - 1) / PH_ROUND);
+  return 205. * rounds < (double)tiles;
+}
+
 hipError_t launch_fusion(int dt, const FusionFfn& f, int layers, int64_t n, int64_t n_keep,
                          const int32_t* kept, int64_t kept_batch, int d_v, const void* r, void* u,
                          void* hidden, hipStream_t st, const int32_t* count) {

@@ -15,6 +15,10 @@ namespace lookme {
 hipError_t launch_project(int dt, const void* x, const void* wt, void* q, int64_t n, int d_in,
                           int d_e, int layers, hipStream_t st);
 
+// Whether a matrix product of `tiles` 256 x 256 output tiles runs on them (the
+// phased kernel of tile_gemm.h) or on 64 x 64 ones.
+bool product_phased(int dt, int64_t tiles, int64_t k_bytes);
+
 // ---- library-owned scratch (noalloc.hip) ---------------------------------
 // lookme_inject_noalloc keeps the criticality keys of up to
 // LOOKME_NOALLOC_MAX_ROWS rows and, when the caller passes no kept_out, the

@@ -38,6 +38,7 @@
 
 #include "common.h"
 #include "dtl.h"
+#include "kernels.h"
 #include "phase_gemm.h"
 
 namespace lookme {
@@ -634,30 +635,17 @@ template <int EPI>
 hipError_t launch_tile_gemm(int dt, TileGemmParams p, int batches, hipStream_t st) {
   // column-major tile order when B has at least as many rows as A
   p.col_major = (int64_t)p.cols * (EPI == EPI_SWIGLU ? 2 : 1) >= p.rows;
-  // The phased kernel from 48 tiles of 256 x 256 on (192 quarters): 2304 x
-  // 2048 x 2048 for four layers 310 -> 149 us (gate/up) and 147 -> 85 us
-  // (down), 512 x 2048 x 2048 for four layers (64 tiles) 31 -> 24.5 us;
-  // below it too few of the CUs get one: 1024 x 2048 x 2048 (32 tiles) 17.2
-  // us here, 18.0 phased, 512 x 2048 x 2048 13.2 and 16.5.  float32 is bound
-  // by the matrix cores on either, and 64 x 64 tiles fill the last round
-  // better: from 512 tiles on (16384 x 2048 x 1024 607 -> 561 us; 8192 x 1024
-  // x 1024, 128 tiles, 166 and 172).
-  // Short sums (K of at most 1 KiB a row) are over before the deeper pipeline
-  // pays, so they take it where most of a round is whole tiles (relevance
-  // lookups of 20011 rows, 158 tiles, 131.9 us here and 129.1 phased; of
-  // 12000, 94 tiles, 125.2 and 132.2; 4000 x 2048 x 512, 128, 19.0 and 20.5).
-  // Its lane offsets are 32-bit: rows below 8 MiB, gathered rows inside 4 GiB.
+  // The phased kernel's lane offsets are 32-bit: rows below 8 MiB, gathered
+  // rows inside 4 GiB.
   const bool near = p.a_bytes < (8 << 20) && p.k_bytes < (8 << 20) && p.b_ld < (8 << 20) &&
                     (p.a_sel == nullptr || p.sel_rows * p.a_bytes < ((int64_t)1 << 32));
-  const int64_t large = phase_tiles<EPI>(p, batches);
-  if (p.cols % 8 == 0 && near && large >= (dt != DT_BF16 ? 512 : p.k_bytes > 1024 ? 48 : 129)) {
+  if (p.cols % 8 == 0 && near && product_phased(dt, phase_tiles<EPI>(p, batches), p.k_bytes))
     return launch_phase<EPI>(dt, p, batches, st);
-  }
   if constexpr (EPI != EPI_SWIGLU) {
     // 32-row tiles while every one has a CU of its own and 64-row ones leave
     // half of the CUs idle: a CU's LDS traffic a stage (which bounds these)
-    // falls from 48 to 36 KiB.  Image fused
-      // injection 30.3 -> 27.4 us, propagated 95.7 -> 89.2 (same sums, same bits).
+    // falls from 48 to 36 KiB.  Image fused injection 30.3 -> 27.4 us,
+    // propagated 95.7 -> 89.2 (same sums, same bits).
     const int tiles32 = (int)((p.rows + 31) / 32 * ((p.cols + 63) / 64));
     if ((int64_t)tiles32 * batches <= 256) {
       p.tiles = tiles32;
