@@ -103,24 +103,19 @@ __device__ __forceinline__ void tile_origin(const TileGemmParams& a, int tile, i
 
 __device__ __forceinline__ float silu_f(float x) { return x / (1.f + expf(-x)); }
 
-// Epilogue of a tile (tile index `tile` of batch z) from the accumulators of
+// Epilogue of the tile at (m0, n0) of batch z from the accumulators of
 // thread tid: the lane holds rows m0 + wm + 16 i + 4 g + r and tile columns
 // wn + 16 j + n16.  xch: 4096 floats of LDS (EPI_SWIGLU only).
 template <int DT, int EPI, int TI>
 __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
-                                              f32x4_t (&acc)[TI][2],
-                                              int64_t z, int tile, int tid, float* xch,
-                                              int64_t rows) {
-  using S = TgShapeT<TI>;
+                                              f32x4_t (&acc)[TI][2], int64_t z, int64_t m0,
+                                              int n0, int tid, float* xch, int64_t rows,
+                                              bool live) {
   constexpr int MI = TI, NJ = 2, WN = 2;
   constexpr int ES = DT == DT_BF16 ? 2 : 4;
-  constexpr int TCOLS = EPI == EPI_SWIGLU ? S::BN / 2 : S::BN;
   const int lane = tid & 63, wv = tid >> 6;
   const int n16 = lane & 15, g = lane >> 4;
   const int wm = (wv / WN) * 16 * MI, wn = (wv % WN) * 16 * NJ;
-  int64_t m0;
-  int n0;
-  tile_origin<TI>(a, tile, TCOLS, &m0, &n0);
   if constexpr (EPI == EPI_SWIGLU) {
     // the up half (waves with wn = 32) passes its tile through LDS to the
     // gate half (wn = 0) of the same rows
@@ -135,7 +130,7 @@ __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
             xch[(((wv / WN) * MI * NJ + i * NJ + j) * 4 + r) * WAVE + lane] = acc[i][j][r];
     }
     __syncthreads();
-    if (wn != 0) return;
+    if (wn != 0 || !live) return;
     char* U = a.out + z * a.out_batch;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
@@ -157,6 +152,7 @@ __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
         }
     }
   } else {
+    if (!live) return;
     // every load (biases, kept rows, H or residual values) is issued before
     // the first store: as far as the compiler knows a store may alias a later
     // load, which would otherwise serialise the elements one round trip each.
@@ -253,31 +249,22 @@ __device__ __forceinline__ void tile_epilogue(const TileGemmParams& a,
   }
 }
 
-template <int DT, int EPI, int NS, int TI = 2>
-__global__ __launch_bounds__(256) void tile_gemm_kernel(TileGemmParams a) {
+// Tile (m0, n0) of batch z, computed by the four waves of threads tid = 0 ..
+// 255 on a ring of NS stages at lds.  live: false for a tile that is computed
+// beside another workgroup half's only to keep its barriers, and not stored.
+template <int DT, int EPI, int NS, int TI>
+__device__ __forceinline__ void tile_gemm_tile(const TileGemmParams& a,
+                                               char (*lds)[TgShapeT<TI>::STAGE], int64_t z,
+                                               int64_t m0, int n0, int tid, int64_t rows,
+                                               bool live) {
   using S = TgShapeT<TI>;
   constexpr int MI = TI, NJ = 2, KB = TG_KB, KSL = KB / 64, WN = 2;
   constexpr int TCOLS = EPI == EPI_SWIGLU ? S::BN / 2 : S::BN;   // output columns a tile
   static_assert(NS >= 2, "a stage in flight while one is multiplied");
-  __shared__ __attribute__((aligned(1024))) char lds[NS][S::STAGE];
-  const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n16 = lane & 15, g = lane >> 4;
   const int wm = (wv / WN) * 16 * MI, wn = (wv % WN) * 16 * NJ;
-  const int64_t z = blockIdx.y;
-
-  const int tile = xcd_remap(blockIdx.x, a.tiles);
-  if (tile < 0) return;
-  int64_t m0;
-  int n0;
-  tile_origin<TI>(a, tile, TCOLS, &m0, &n0);
-  int64_t rows = a.rows;   // live rows of this batch
-  if (a.count != nullptr) {
-    const int64_t c = a.count[z * a.count_step];
-    rows = c < rows ? c : rows;
-    if (m0 >= rows) return;   // the whole workgroup: no barrier is left waiting
-  }
   const int nst = (int)(a.k_bytes / KB);
   const char* A0 = a.a0 + z * a.a_batch;
   const char* B0 = a.b + z * a.b_batch;
@@ -400,7 +387,28 @@ __global__ __launch_bounds__(256) void tile_gemm_kernel(TileGemmParams a) {
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into LDS outlives the wave
 
-  tile_epilogue<DT, EPI, TI>(a, acc, z, tile, tid, reinterpret_cast<float*>(&lds[0][0]), rows);
+  tile_epilogue<DT, EPI, TI>(a, acc, z, m0, n0, tid, reinterpret_cast<float*>(&lds[0][0]), rows,
+                             live);
+}
+
+template <int DT, int EPI, int NS, int TI = 2>
+__global__ __launch_bounds__(256) void tile_gemm_kernel(TileGemmParams a) {
+  using S = TgShapeT<TI>;
+  constexpr int TCOLS = EPI == EPI_SWIGLU ? S::BN / 2 : S::BN;
+  __shared__ __attribute__((aligned(1024))) char lds[NS][S::STAGE];
+  const int64_t z = blockIdx.y;
+  const int tile = xcd_remap(blockIdx.x, a.tiles);
+  if (tile < 0) return;
+  int64_t m0;
+  int n0;
+  tile_origin<TI>(a, tile, TCOLS, &m0, &n0);
+  int64_t rows = a.rows;   // live rows of this batch
+  if (a.count != nullptr) {
+    const int64_t c = a.count[z * a.count_step];
+    rows = c < 0 ? 0 : (c < a.rows ? c : a.rows);
+    if (m0 >= rows) return;
+  }
+  tile_gemm_tile<DT, EPI, NS, TI>(a, lds, z, m0, n0, threadIdx.x, rows, true);
 }
 
 // ---------------------------------------------------------------------------
@@ -543,6 +551,18 @@ __device__ __forceinline__ void phase_tile(const TileGemmParams& a, char* lds, i
   }
 }
 
+// A counted product with at most PH_FEW live tiles (512 of 64 x 64) runs on
+// those instead, each on four waves: one a CU while there are that many CUs,
+// then two (a half of the waves and of the LDS each).  A product's launch is
+// chosen by its capacity, and a gate that opens few rows would leave most of
+// the CUs idle and, in float32, the matrix cores of the others busy with
+// padding (50 of 23040 rows open: float32 fused injection 193 -> 71 us,
+// multi-scale 129 -> 47, bf16 24 -> 19; 500 open 199 -> 80, 137 -> 54, 29 -> 25).
+// bf16 over several layers keeps the phased tiles: each 64 x 64 tile of a row
+// block streams weights of its own, and the deeper pipeline is the better at
+// that (four layers, 50 rows, 61 us against 74).
+constexpr int PH_FEW = 32;
+
 // Tiles are numbered batch by batch, inside a batch the column tiles of one
 // row block after another (column-major was slower at every shape measured:
 // 32768 x 512 x 4096 113 against 142 us), and dealt to the XCDs in contiguous
@@ -560,39 +580,77 @@ __global__ __launch_bounds__(512, 2) void phase_gemm_kernel(TileGemmParams a) {
     const int64_t c = a.count[z * a.count_step];
     return c < 0 ? 0 : (c < a.rows ? c : a.rows);
   };
-  auto tiles_of = [&](int64_t rows) { return (int)((rows + S::BM - 1) / S::BM) * tn; };
-  int total = 0;
-  if (a.count == nullptr || a.count_step == 0) total = tiles_of(live(0)) * a.batches;
-  else
-    for (int z = 0; z < a.batches; ++z) total += tiles_of(live(z));
+  // the batches' live rows in tiles of bm rows, tc tiles across
+  auto count_tiles = [&](int bm, int tc) {
+    if (a.count == nullptr || a.count_step == 0)
+      return (int)((live(0) + bm - 1) / bm) * tc * a.batches;
+    int t = 0;
+    for (int z = 0; z < a.batches; ++z) t += (int)((live(z) + bm - 1) / bm) * tc;
+    return t;
+  };
+  // batch, live rows, tile row and tile column of such a tile's number
+  // (quotients come out of vector instructions: said to be uniform, so that
+  // the operands' bases stay in scalar registers)
+  auto find_tile = [&](int tile, int bm, int tc, int& z, int64_t& rows, int& tr, int& col) {
+    z = 0;
+    rows = live(0);
+    if (a.count == nullptr || a.count_step == 0) {
+      const int per = (int)((rows + bm - 1) / bm) * tc;
+      z = __builtin_amdgcn_readfirstlane(tile / per);
+      tile -= z * per;
+    } else {
+      for (int per = (int)((rows + bm - 1) / bm) * tc; tile >= per;
+           per = (int)((rows + bm - 1) / bm) * tc) {
+        tile -= per;
+        rows = live(++z);
+      }
+    }
+    tr = __builtin_amdgcn_readfirstlane(tile / tc);
+    col = tile - tr * tc;
+  };
+  const int total = count_tiles(S::BM, tn);
+  int z, tr, tc;
+  int64_t rows;
+  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_RESID || EPI == EPI_ADD || EPI == EPI_STORE) {
+    if (a.count != nullptr && total <= PH_FEW && (DT == DT_F32 || a.batches == 1)) {
+      using T = TgShapeT<2>;
+      static_assert(S::BUF == 4 * T::STAGE, "a ring of four stages for each half");
+      constexpr int TC = EPI == EPI_SWIGLU ? T::BN / 2 : T::BN;
+      const int across = (a.cols + TC - 1) / TC;
+      const int units = count_tiles(T::BM, across);
+      char (*ring)[T::STAGE] = reinterpret_cast<char (*)[T::STAGE]>(lds);
+      const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+      if (units <= PH_ROUND) {
+        // a CU each: the other four waves end (a barrier waits for the
+        // surviving waves only), their LDS deepens the ring
+        const int unit = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, units));
+        if (unit < 0 || half != 0) return;
+        find_tile(unit, T::BM, across, z, rows, tr, tc);
+        tile_gemm_tile<DT, EPI, 8, 2>(a, ring, z, (int64_t)tr * T::BM, tc * TC, threadIdx.x & 255,
+                                      rows, true);
+        return;
+      }
+      const int pair = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, (units + 1) / 2));
+      if (pair < 0) return;
+      const bool own = 2 * pair + half < units;   // else the pair's first tile, not stored
+      find_tile(own ? 2 * pair + half : 2 * pair, T::BM, across, z, rows, tr, tc);
+      tile_gemm_tile<DT, EPI, 4, 2>(a, ring + 4 * half, z, (int64_t)tr * T::BM, tc * TC,
+                                    threadIdx.x & 255, rows, own);
+      return;
+    }
+  }
   const PhasePlan pl = phase_plan(total);
   const int first_cut = (pl.whole + 7) / 8 * 8;   // workgroups of the whole tiles
   const bool whole = (int)blockIdx.x < first_cut;
   int tile = whole ? xcd_remap(blockIdx.x, pl.whole)
                    : xcd_remap((int)blockIdx.x - first_cut, 4 * pl.cut);
   if (tile < 0) return;
-  // (quotients come out of vector instructions: said to be uniform, so that
-  // the operands' bases stay in scalar registers)
   tile = __builtin_amdgcn_readfirstlane(tile);
   const int quarter = tile & 3;
   if (!whole) tile = pl.whole + (tile >> 2);
-  int z = 0;
-  int64_t rows = live(0);
-  if (a.count == nullptr || a.count_step == 0) {
-    const int per = tiles_of(rows);
-    z = __builtin_amdgcn_readfirstlane(tile / per);
-    tile -= z * per;
-  } else {
-    for (int per = tiles_of(rows); tile >= per; per = tiles_of(rows)) {
-      tile -= per;
-      rows = live(++z);
-    }
-  }
-  int64_t m0;
-  int n0;
-  const int tm = __builtin_amdgcn_readfirstlane(tile / tn);
-  m0 = (int64_t)tm * S::BM;
-  n0 = (tile - tm * tn) * TCOLS;
+  find_tile(tile, S::BM, tn, z, rows, tr, tc);
+  int64_t m0 = (int64_t)tr * S::BM;
+  int n0 = tc * TCOLS;
   if (whole) {
     phase_tile<DT, EPI, 4, 2>(a, lds, z, rows, m0, n0);
   } else {
