@@ -9,10 +9,10 @@
 //                squares, accumulated in a fixed order; stored as its bit
 //                pattern, it orders like the norm (non-negative floats order
 //                like their bits, and the square root keeps the order);
-//   select_layer one workgroup (1024 or 256 threads): 4-pass MSB-first radix
-//                select of the n_keep-th largest key (keys cached in LDS when
-//                they fit), then an order-preserving compaction (ballots and
-//                prefix sums) of the kept token ids;
+//   select_layer one workgroup (1024, 512 or 256 threads): MSB-first radix
+//                select of the n_keep-th largest key in at most four passes
+//                (keys cached in LDS when they fit), then an order-preserving
+//                compaction (ballots and prefix sums) of the kept token ids;
 //   row_dot, gate_compact_layer  the learned SKA gate's logit z = Delta_i W_g
 //                and the ascending compaction of its open rows (Eq. 9).
 #pragma once

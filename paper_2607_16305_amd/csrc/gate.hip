@@ -9,11 +9,11 @@
 //                 (HBM-bound; four 16-byte loads in flight per lane) against
 //                 the layer's W_g column (L2-resident), fp32 fused
 //                 multiply-adds in a fixed order, one float z per row;
-//   gate_compact  one workgroup per layer: every thread owns 32 consecutive
-//                 rows (their signs packed in one register), a block prefix
-//                 sum of the per-thread counts gives each open row its slot,
-//                 so the list comes out ascending without sorting; the tail
-//                 of the list is filled with -1 and the count stored.
+//   gate_compact  one workgroup per layer: a wave owns consecutive groups of
+//                 64 rows, whose signs are one ballot each; prefix sums of the
+//                 counts give each open row its slot, so the list comes out
+//                 ascending without sorting (crit.h); the tail of the list is
+//                 filled with -1 and the count stored.
 #include "common.h"
 #include "crit.h"
 #include "kernels.h"

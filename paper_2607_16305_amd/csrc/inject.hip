@@ -7,10 +7,11 @@
 //               the fp32 sum of squares as its bit pattern (non-negative
 //               floats order like their bits, and the square root keeps the
 //               order, so selecting on it selects on the norm);
-//   crit_select one workgroup per layer: 4-pass MSB-first radix select of
-//               the n_keep-th largest key (keys cached in LDS when they
-//               fit), then an order-preserving compaction (block prefix
-//               sums) of the kept token ids;
+//   crit_select one workgroup per layer: MSB-first radix select of the
+//               n_keep-th largest key (keys cached in LDS when they fit), then
+//               an order-preserving compaction of the kept token ids (crit.h);
+//   ms_mix      one workgroup per kept token: the multi-scale router's mix of
+//               the token's rows (multiscale.hip);
 //   inject      one workgroup per kept token (one thread per 16-byte chunk of
 //               a row, up to 256): coalesced loads of its k table rows (all
 //               in flight together), fp32 weighted sum in a fixed order, one

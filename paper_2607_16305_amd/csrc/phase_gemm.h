@@ -17,12 +17,13 @@
 // own phase.  The loads are buffer loads (load_lds16_at): with 64-bit
 // addresses each took vector instructions and two registers beside the 240
 // that accumulators and fragments fill (23040 x 2048 x 2048 193.7 -> 185.5
-// us, 1042 TFLOP/s; 32768 x 512 x 4096 113 us, 1216).  What bounds it now:
-// without the loads 98 us of those 113, without the products 76, so the
-// stage stream out of L2 and the LDS it shares with the fragment reads.  The weights' rows are MFMA operand A and the tokens' rows
-// operand B, with the weight rows of the NJ tiles of a wave dealt so that a
-// lane ends with 4 NJ neighbouring columns of one output row: the epilogues
-// read and write 16 bytes a lane.
+// us, 1042 TFLOP/s; 32768 x 512 x 4096, a shape that the projection's own
+// kernel takes beside another stream, 113 us, 1216).  What bounds it: without
+// the loads 98 us of those 113, without the products 76, so the stage stream
+// out of L2 and the LDS it shares with the fragment reads.  The weights' rows
+// are MFMA operand A and the tokens' rows operand B, with the weight rows of
+// the NJ tiles of a wave dealt so that a lane ends with 4 NJ neighbouring
+// columns of one output row: the epilogues read and write 16 bytes a lane.
 #pragma once
 
 #include "common.h"

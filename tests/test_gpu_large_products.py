@@ -1,7 +1,7 @@
 """Products large enough for the phased matrix-core kernel (256 x 256 tiles),
 at the sizes where its tiling can go wrong: one K stage and an odd number of
 them, ragged row and column edges, batches whose tiles all lie in the cut last
-round and ones with whole tiles before it, float32, and
+round and ones with whole tiles before it, float32, every epilogue, and
 counted kept lists (tiles numbered from the device's counts), down to the few
 live tiles that run on 64 x 64 ones.  Against the oracle with the bounds of
 its checks, or against float64 with a bound from the roundings on the way.
@@ -14,7 +14,8 @@ import numpy as np
 import pytest
 import torch
 
-from synth import Workload, make_fusion, make_gate, make_inputs
+from synth import (Workload, make_fusion, make_gate, make_inputs, make_propagation,
+                   make_relevance)
 
 pytestmark = pytest.mark.gpu
 
@@ -84,6 +85,40 @@ def test_fused_injection_on_large_tiles(name):
         np.random.default_rng(21).choice(wl.n_tokens, 40, replace=False), kept0[:10],
         kept0[max(0, last - 9):last + 1], kept0[250:262]]))
     rep = (check_gated_run if counted else check_fused_run)(r, tokens=toks)
+    assert rep.ok, str(rep)
+
+
+def test_propagation_on_large_tiles():
+    """The propagation product with its residual: 1500 rows of 2048 columns
+    and a ragged last tile, 48 tiles."""
+    from tests.harness import PropagatedRun, check_propagated_run
+    wl = Workload("lp_p", "bf16", 3000, 2, 64, 64, 20, 60, 1984, 1992, 4, 50, usage="uniform",
+                  value_std=1.0)
+    print(f"[large-products] propagation: {wl}", flush=True)
+    assert _phased("bf16", wl.n_keep, wl.d_v, wl.d_v)
+    inp = make_inputs(wl, seed=23, device=DEV)
+    fus = make_fusion(wl, 23, 512, device=DEV)
+    r = PropagatedRun(inp, fus, make_propagation(wl, 23, 1, device=DEV)).run()
+    kept0 = r.kept[0].cpu().numpy()
+    rep = check_propagated_run(r, tokens=np.unique(np.concatenate([kept0[:8], kept0[-8:],
+                                                                   kept0[252:260]])))
+    assert rep.ok, str(rep)
+
+
+@pytest.mark.parametrize("dtype,n,hidden,P", [("bf16", 2100, 1024, 1496),
+                                              ("f32", 6200, 352, 2200)])
+def test_relevance_logits_on_large_tiles(dtype, n, hidden, P):
+    """The relevance MLP's second layer where it is a product of its own (a
+    width that the fused top-k does not take), with its bias, ragged edges."""
+    from tests.harness import RelevanceRun, check_relevance_run
+    wl = Workload("lp_r", dtype, n, 1, 64, 64, 9, P, 64, 64, 8, 10, usage="uniform")
+    print(f"[large-products] relevance: {wl} hidden {hidden}", flush=True)
+    assert _phased(dtype, n, P, hidden)
+    inp = make_inputs(wl, seed=25, device=DEV)
+    r = RelevanceRun(inp, make_relevance(wl, 25, hidden, device=DEV)).run()
+    toks = np.unique(np.concatenate([np.arange(8), np.arange(n - 8, n), np.arange(250, 262),
+                                     np.random.default_rng(25).choice(n, 60, replace=False)]))
+    rep = check_relevance_run(r, tokens=toks)
     assert rep.ok, str(rep)
 
 
