@@ -120,6 +120,7 @@ struct SelLds {
   int need;
   int total;
   int listed;
+  uint32_t ranked;
 };
 
 // Bits of m below the calling lane's.
@@ -275,7 +276,10 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
       sl.need = need - (cum - h);
       sl.total = h;
     }
-    if (tid == 0) sl.listed = 0;
+    if (tid == 0) {
+      sl.listed = 0;
+      sl.ranked = 0xFFFFFFFFu;
+    }
     __syncthreads();
     prefix = sl.prefix;
     need = sl.need;
@@ -290,7 +294,6 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
           if (at < LIST) hist[at] = (int)k;
         }
       });
-      if (tid == 0) sl.prefix = 0xFFFFFFFFu;
       __syncthreads();
       uint32_t x = 0;
       int gt = 0;
@@ -298,12 +301,12 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
         x = (uint32_t)hist[tid];
 #pragma unroll 8
         for (int j = 0; j < left; ++j) gt += (uint32_t)hist[j] > x;
-        if (gt < need) atomicMin(&sl.prefix, x);
+        if (gt < need) atomicMin(&sl.ranked, x);
       }
       __syncthreads();
-      if (tid < left && x == sl.prefix) sl.total = need - gt;   // equal keys: equal values
+      if (tid < left && x == sl.ranked) sl.total = need - gt;   // equal keys: equal values
       __syncthreads();
-      prefix = sl.prefix;
+      prefix = sl.ranked;
       need = sl.total;
       break;
     }
@@ -338,10 +341,13 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
   e = __builtin_amdgcn_readfirstlane(e);
   each([&](int i, uint32_t k) {
     const uint64_t mg = __ballot(k > T), me = __ballot(k == T);
-    const int eb = e + bits_below(me);
+    int eb = e;
+    if (me != 0) {
+      eb += bits_below(me);
+      e += __popcll(me);
+    }
     const int at = g + bits_below(mg) + min(eb, take_eq);
     if ((k > T || (k == T && eb < take_eq)) && at < n_keep) kept[at] = i;
-    e += __popcll(me);
     g += __popcll(mg);
   });
 }
