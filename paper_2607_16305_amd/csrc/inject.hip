@@ -170,7 +170,7 @@ __global__ __launch_bounds__(INJ_THREADS) void inject_kernel(
 // 11520 rows 1091 us on one group, 952 on two).  launch_multiscale has the rows
 // that gather first (ms_gathers).
 constexpr int MS_GROUP = 256;              // threads of a scale at most
-constexpr int64_t MS_WIDE = 262144, MS_NARROW = 393216;   // threads of a launch
+constexpr int64_t MS_WIDE = 327680, MS_NARROW = 393216;   // threads of a launch
 constexpr int64_t MS_CU_LDS = 160 * 1024, MS_CU_THREADS = 1280;
 constexpr int MS_ROW_THREADS = 1024;       // threads of a row at most
 
