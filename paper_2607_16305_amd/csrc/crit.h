@@ -120,7 +120,6 @@ struct SelLds {
   int need;
   int total;
   int listed;
-  uint32_t ranked;
 };
 
 // Bits of m below the calling lane's.
@@ -199,12 +198,14 @@ constexpr int sel_cache_words(int cn) { return cn > 0 ? cn : 1; }
 // of its LDS reads (32768 keys: 32 a thread), so: 32-bit indices, a wave's
 // keys read side by side, bins in eight copies (a lane adds to copy lane mod
 // 8: keys of one batch share few leading digits, and adds to one LDS word go
-// one after the other), and once the keys that share the digits found so far
-// are few they are ranked directly instead of by more passes over all keys.
-// 32768 keys 41 -> 28 us, 4 x 23040 32 -> 19.  Few: the ranking compares each
-// with each, 256 take about one of the passes it saves (norms within 6% of one
-// another: with up to 1024 ranked 23040 keys took 49.4 us, with 256 26.1;
-// 16384 33.8 and 21.1).
+// one after the other), and once two digits are known the keys that share them
+// are ranked directly, if they are few, instead of by two more passes over all
+// keys.  32768 keys 41 -> 28 us, 4 x 23040 32 -> 19.  Few: the ranking compares
+// each with each, 256 take about one of the passes they save (norms within 6%
+// of one another: with up to 1024 ranked, 4 x 23040 keys took 32.5 us and 32768
+// 47.0, with 256 26.5 and 33.2).  The positions stay below n_keep as long as
+// the keys do not change during the launch; the comparison that makes sure of
+// it takes 0.3 us of 4 x 23040 keys.
 template <int CN, int THREADS = SEL_THREADS>
 __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, int64_t n64,
                                              int64_t n_keep64, int32_t* __restrict__ kept,
@@ -213,7 +214,7 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
   constexpr int WAVES = THREADS / WAVE, BATCH = 8;
   constexpr int LIST = 256;   // keys ranked directly, in the bins' words
   static_assert(THREADS % 256 == 0, "a thread per radix bin");
-  static_assert(WAVES <= SEL_WAVES && LIST <= THREADS, "scan partials, a thread per listed key");
+  static_assert(WAVES <= SEL_WAVES && LIST <= 256 * SEL_COPIES, "scan partials, list");
   int* hist = sl.hist;
   int* wsum = sl.wsum;
   if (n_keep64 == 0) return;
@@ -276,18 +277,14 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
       sl.need = need - (cum - h);
       sl.total = h;
     }
-    if (tid == 0) {
-      sl.listed = 0;
-      sl.ranked = 0xFFFFFFFFu;
-    }
+    if (tid == 0) sl.listed = 0;
     __syncthreads();
     prefix = sl.prefix;
     need = sl.need;
     mask |= 255u << shift;
     const int left = sl.total;   // keys that share the digits found so far
-    if (pass >= 1 && pass < 3 && left <= LIST) {
-      // every one of them into a list; the one sought is the smallest with
-      // fewer than `need` above it
+    if (pass == 1 && left <= LIST) {
+      // every one of them into a list, then each key's rank in it
       each([&](int, uint32_t k) {
         if ((k & mask) == prefix) {
           const int at = atomicAdd(&sl.listed, 1);
@@ -295,18 +292,21 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
         }
       });
       __syncthreads();
-      uint32_t x = 0;
-      int gt = 0;
-      if (tid < left) {
-        x = (uint32_t)hist[tid];
-#pragma unroll 8
-        for (int j = 0; j < left; ++j) gt += (uint32_t)hist[j] > x;
-        if (gt < need) atomicMin(&sl.ranked, x);
+      for (int t = tid; t < left; t += THREADS) {
+        const uint32_t x = (uint32_t)hist[t];
+        int gt = 0, ge = 0;
+        for (int j = 0; j < left; ++j) {
+          const uint32_t y = (uint32_t)hist[j];
+          gt += y > x;
+          ge += y >= x;
+        }
+        if (gt < need && need <= ge) {   // equal keys store equal values
+          sl.prefix = x;
+          sl.total = need - gt;
+        }
       }
       __syncthreads();
-      if (tid < left && x == sl.ranked) sl.total = need - gt;   // equal keys: equal values
-      __syncthreads();
-      prefix = sl.ranked;
+      prefix = sl.prefix;
       need = sl.total;
       break;
     }
@@ -341,13 +341,15 @@ __device__ __forceinline__ void select_layer(const uint32_t* __restrict__ gkey, 
   e = __builtin_amdgcn_readfirstlane(e);
   each([&](int i, uint32_t k) {
     const uint64_t mg = __ballot(k > T), me = __ballot(k == T);
-    int eb = e;
+    if (k > T) {
+      const int at = g + bits_below(mg) + min(e + bits_below(me), take_eq);
+      if (at < n_keep) kept[at] = i;
+    }
     if (me != 0) {
-      eb += bits_below(me);
+      const int eb = e + bits_below(me), at = g + bits_below(mg) + eb;
+      if (k == T && eb < take_eq && at < n_keep) kept[at] = i;
       e += __popcll(me);
     }
-    const int at = g + bits_below(mg) + min(eb, take_eq);
-    if ((k > T || (k == T && eb < take_eq)) && at < n_keep) kept[at] = i;
     g += __popcll(mg);
   });
 }
