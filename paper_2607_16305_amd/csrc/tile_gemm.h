@@ -611,33 +611,34 @@ __global__ __launch_bounds__(512, 2) void phase_gemm_kernel(TileGemmParams a) {
   const int total = count_tiles(S::BM, tn);
   int z, tr, tc;
   int64_t rows;
-  if constexpr (EPI == EPI_SWIGLU || EPI == EPI_RESID || EPI == EPI_ADD || EPI == EPI_STORE) {
-    if (a.count != nullptr && total <= PH_FEW && (DT == DT_F32 || a.batches == 1)) {
-      using T = TgShapeT<2>;
-      static_assert(S::BUF == 4 * T::STAGE, "a ring of four stages for each half");
-      constexpr int TC = EPI == EPI_SWIGLU ? T::BN / 2 : T::BN;
-      const int across = (a.cols + TC - 1) / TC;
-      const int units = count_tiles(T::BM, across);
-      char (*ring)[T::STAGE] = reinterpret_cast<char (*)[T::STAGE]>(lds);
-      const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-      if (units <= PH_ROUND) {
-        // a CU each: the other four waves end (a barrier waits for the
-        // surviving waves only), their LDS deepens the ring
-        const int unit = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, units));
-        if (unit < 0 || half != 0) return;
-        find_tile(unit, T::BM, across, z, rows, tr, tc);
-        tile_gemm_tile<DT, EPI, 8, 2>(a, ring, z, (int64_t)tr * T::BM, tc * TC, threadIdx.x & 255,
-                                      rows, true);
-        return;
-      }
-      const int pair = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, (units + 1) / 2));
-      if (pair < 0) return;
-      const bool own = 2 * pair + half < units;   // else the pair's first tile, not stored
-      find_tile(own ? 2 * pair + half : 2 * pair, T::BM, across, z, rows, tr, tc);
-      tile_gemm_tile<DT, EPI, 4, 2>(a, ring + 4 * half, z, (int64_t)tr * T::BM, tc * TC,
-                                    threadIdx.x & 255, rows, own);
+  // (compiled for the products without counts too: without this path the
+  // compiler spilled six registers of their float32 loop, and each reload
+  // waited for every load in flight)
+  if (a.count != nullptr && total <= PH_FEW && (DT == DT_F32 || a.batches == 1)) {
+    using T = TgShapeT<2>;
+    static_assert(S::BUF == 4 * T::STAGE, "a ring of four stages for each half");
+    constexpr int TC = EPI == EPI_SWIGLU ? T::BN / 2 : T::BN;
+    const int across = (a.cols + TC - 1) / TC;
+    const int units = count_tiles(T::BM, across);
+    char (*ring)[T::STAGE] = reinterpret_cast<char (*)[T::STAGE]>(lds);
+    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    if (units <= PH_ROUND) {
+      // a CU each: the other four waves end (a barrier waits for the
+      // surviving waves only), their LDS deepens the ring
+      const int unit = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, units));
+      if (unit < 0 || half != 0) return;
+      find_tile(unit, T::BM, across, z, rows, tr, tc);
+      tile_gemm_tile<DT, EPI, 8, 2>(a, ring, z, (int64_t)tr * T::BM, tc * TC, threadIdx.x & 255,
+                                    rows, true);
       return;
     }
+    const int pair = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, (units + 1) / 2));
+    if (pair < 0) return;
+    const bool own = 2 * pair + half < units;   // else the pair's first tile, not stored
+    find_tile(own ? 2 * pair + half : 2 * pair, T::BM, across, z, rows, tr, tc);
+    tile_gemm_tile<DT, EPI, 4, 2>(a, ring + 4 * half, z, (int64_t)tr * T::BM, tc * TC,
+                                  threadIdx.x & 255, rows, own);
+    return;
   }
   const PhasePlan pl = phase_plan(total);
   const int first_cut = (pl.whole + 7) / 8 * 8;   // workgroups of the whole tiles
