@@ -156,6 +156,9 @@ hipError_t launch_relevance(int dt, const void* q, const int32_t* scene, const f
                             const void* prim_keys, const RelevanceMlp& mlp, int64_t rows, int d_e,
                             int S, int P, int k, void* act, int32_t* prim, float* w,
                             float* logits, hipStream_t st);
+// The ranges of W2 rows per 128-row block of the second layer's 32 x 32 form;
+// 0: none that fits.
+int relevance_ranges32(int64_t rows, int P, int k);
 
 // ---- sparse injection through the SwiGLU fusion (Eq. 10) ----------------
 // Per layer l (tensors borrowed): w_gate, w_up [layers, d_ff, d_v] and

@@ -532,19 +532,40 @@ __global__ __launch_bounds__(256) void relevance_merge_kernel(const uint64_t* __
     }
 }
 
-// Ranges of W2 rows per row block: enough for `units` units (512: the chip's
-// resident workgroups; 256 for the 32 x 32 form, whose list upkeep grows with
-// every range: 12000 rows x 1024, k = 16, 139.8 -> 132.2 us for the
-// whole lookup, 20011 x 1000, k = 8, 129.9 -> 128.4), each range at least 128 rows (and k),
-// and as many as keep a range's b2 within its LDS space; 0 when that takes
-// more than 16.
-static int relevance_splits(int64_t row_blocks, int P, int k, int units = 512) {
-  int splits = 1;
-  while (splits < 16 && row_blocks * splits < units && P / (2 * splits) >= 128 &&
-         P / (2 * splits) >= k)
-    splits *= 2;
+// A range's b2 stays within its LDS space; 0 when that takes more than 16.
+static int ranges_of_lds(int splits, int P) {
   while (splits <= 16 && (P + splits - 1) / splits > RT_MAX_KPS) splits *= 2;
   return splits <= 16 ? splits : 0;
+}
+
+// Ranges of W2 rows per row block in the 16 x 16 form: enough units to fill
+// the chip's 512 resident workgroups, each range at least 128 rows (and k).
+static int relevance_splits(int64_t row_blocks, int P, int k) {
+  int splits = 1;
+  while (splits < 16 && row_blocks * splits < 512 && P / (2 * splits) >= 128 &&
+         P / (2 * splits) >= k)
+    splits *= 2;
+  return ranges_of_lds(splits, P);
+}
+
+// The same for the 32 x 32 form, whose list upkeep grows with every range: as
+// many units as are resident at once, and no more (14000 rows x 1024, k = 16,
+// whole lookup: 8 ranges a row block, 880 units, 136 us; 4, 440 units, 114).
+// The second workgroup of a CU is worth it while the ranges stay long enough
+// for their k best to settle, the first cut, which brings the merge launch,
+// from twice that length (512 hidden units, us, one against two units a CU:
+// 32768 rows x 4096, k = 16, 395 and 329; x 2048, k = 8, 197 and 173; 16384 x
+// 4096, k = 16, 241 and 208, x 512, 100 and 103; 28000 x 512, 134 and 140).
+int relevance_ranges32(int64_t rows, int P, int k) {
+  const int64_t blocks = (rows + 127) / 128;
+  int splits = 1;
+  while (splits < 16 && blocks * 2 * splits <= 512) {
+    const int range = P / (2 * splits);
+    if (range < 128 || range < k) break;
+    if (blocks * 2 * splits > 256 && range < (splits == 1 ? 32 : 16) * k) break;
+    splits *= 2;
+  }
+  return ranges_of_lds(splits, P);
 }
 
 // The split's lists merged per row (nothing to do for one range).
@@ -590,7 +611,7 @@ template <int KS, int KL, int WAVES>
 static hipError_t launch_topk32(const RelTopkParams& p0, float* part_ws, hipStream_t st) {
   RelTopkParams p = p0;
   const int64_t row_blocks = (p.rows + 32 * WAVES - 1) / (32 * WAVES);
-  p.splits = relevance_splits(row_blocks, p.P, p.k, 256);
+  p.splits = relevance_ranges32(p.rows, p.P, p.k);
   if (p.splits < 1) return hipErrorInvalidValue;
   p.kps = ((p.P + p.splits - 1) / p.splits + 31) / 32 * 32;
   p.splits = (p.P + p.kps - 1) / p.kps;   // no empty range

@@ -1,7 +1,7 @@
 """The rules that choose a kernel by size, called in the built library (they
 are host code; no GPU is used): routing in the scoring kernel's shared mode or
-in the tile kernel, the partials that its splits need, and the products that
-run on 256 x 256 tiles."""
+in the tile kernel, the partials that its splits need, the products that
+run on 256 x 256 tiles, and the ranges of the relevance MLP's second layer."""
 
 import ctypes
 
@@ -116,3 +116,38 @@ def test_a_workspace_serves_every_smaller_batch(dt, S, key_bytes, score):
 ])
 def test_products_on_large_tiles(dt, tiles, k_bytes, phased):
     assert product_phased(dt, tiles, k_bytes) == phased
+
+
+def relevance_ranges(rows, P, k):
+    f = lk.load()._ZN6lookme18relevance_ranges32Elii
+    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    f.restype = ctypes.c_int
+    return f(rows, P, k)
+
+
+@pytest.mark.parametrize("rows,P,k,ranges", [
+    # two workgroups a CU also where one a CU is whole (with one the Zipf
+    # batch's lookup took 395 us against 329)
+    (32768, 4096, 16, 2), (32768, 1024, 8, 2), (16384, 4096, 16, 4), (16384, 2048, 8, 4),
+    (8192, 4096, 16, 8), (4096, 4096, 16, 16),
+    (32769, 4096, 16, 1), (16385, 4096, 16, 2), (20011, 1000, 8, 2), (12000, 1024, 16, 4),
+    # ranges too short for the second one
+    (16384, 512, 16, 2), (32768, 512, 16, 1), (28000, 256, 8, 1), (8192, 1024, 16, 4),
+    # as many as a range's b2 needs
+    (65536, 4097, 8, 2), (65536, 65536, 8, 16), (65536, 65537, 8, 0),
+])
+def test_relevance_ranges(rows, P, k, ranges):
+    assert relevance_ranges(rows, P, k) == ranges
+
+
+def test_relevance_ranges_hold_their_lists():
+    """A split's lists, k entries of 8 bytes a range and row, fit the logits'
+    4 P bytes a row that hold them (the launcher refuses others), and no
+    range is shorter than its k."""
+    for rows in (4096, 4097, 6000, 8192, 16384, 20011, 32768, 32769, 65536):
+        for P in (1, 16, 127, 128, 255, 256, 257, 511, 1000, 1024, 4095, 4096, 5000, 65536):
+            for k in (1, 4, 7, 8, 16):
+                s = relevance_ranges(rows, P, k)
+                assert s >= 1
+                assert s == 1 or (s * k * 2 <= P and P // s >= max(k, 128))
+                assert s == 1 or (rows + 127) // 128 * s <= 512 or -(-P // (s // 2)) > 4096
