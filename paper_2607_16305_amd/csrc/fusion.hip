@@ -29,17 +29,29 @@ namespace lookme {
 // of a round is whole tiles (relevance lookups of 20011 rows, 158 tiles, 131.9
 // us on 64 x 64 tiles and 129.1 phased; of 12000, 94 tiles, 125.2 and 132.2;
 // 4000 x 2048 x 512, 128, 19.0 and 20.5).
-// float32 is bound by the matrix cores on either, and 64 x 64 tiles fill a last
-// round better: a round of whole phased tiles takes as long as 205 tiles'
-// worth of them, a round of quarters 0.35 of that (projection of 256 tiles,
-// K of 8 KiB, 616 us on 64 x 64 tiles, half of 512 tiles' 966 phased; fused
-// injection of 4000 rows x 2048 x 2048, 256 and 128 tiles, 953 -> 829 us).
-bool product_phased(int dt, int64_t tiles, int64_t k_bytes) {
-  if (dt == DT_BF16) return tiles >= (k_bytes > 1024 ? 48 : 129);
+// A last row or column tile that is mostly padding costs a whole one, and 64 x
+// 64 tiles fill a last round better, so the outputs have to be worth the
+// phased kernel's rounds: a round of whole tiles takes as long as `round` whole
+// tiles' worth of 64 x 64 ones (float32, bound by the matrix cores on either,
+// 195; bf16 90, short sums 125), a round of quarters `quarter` of that.  On 64 x
+// 64 tiles and phased: bf16 16385 x 128 x 4096 38 and 57 us, 2 x 600 rows of a
+// fused injection (d_v 1152, d_ff 1600) 38.9 and 43.0, 12000 x 640 x 640
+// of short sums 67.6 and 76.9; 8192 x 320 x 4096 39.5 and 31.6; float32 131072 x
+// 64 x 1024 168 and 483, x 256 632 and 500, 257 rows of four layers (d_v 2048,
+// d_ff 4096) 601 and 694, 12000 x 1024 x 2048 (188 tiles) 462 and 469, 16385 x
+// 768 x 2048 (193) 496 and 473, 4096 x 2048 x 2048 (128) 314 and 252.
+bool product_phased(int dt, int64_t rows, int64_t cols, int tile_cols, int64_t batches,
+                    int64_t k_bytes) {
+  const bool f32 = dt != DT_BF16, brief = k_bytes <= 1024;
+  const int64_t tiles = (rows + 255) / 256 * ((cols + tile_cols - 1) / tile_cols) * batches;
+  if (!f32 && tiles < (brief ? 129 : 48)) return false;
+  const int sub_cols = tile_cols / 4;
+  const int64_t subs = (rows + 63) / 64 * ((cols + sub_cols - 1) / sub_cols) * batches;
   const PhasePlan pl = phase_plan((int)tiles);
+  const double round = f32 ? 195. : brief ? 125. : 90., quarter = f32 ? 0.25 : 0.35;
   const double rounds = (pl.whole + PH_ROUND - 1) / PH_ROUND +
-                        0.35 * ((4 * pl.cut + PH_ROUND - 1) / PH_ROUND);
-  return 205. * rounds < (double)tiles;
+                        quarter * ((4 * pl.cut + PH_ROUND - 1) / PH_ROUND);
+  return 16. * round * rounds < (double)subs;
 }
 
 hipError_t launch_fusion(int dt, const FusionFfn& f, int layers, int64_t n, int64_t n_keep,

@@ -15,9 +15,12 @@ namespace lookme {
 hipError_t launch_project(int dt, const void* x, const void* wt, void* q, int64_t n, int d_in,
                           int d_e, int layers, hipStream_t st);
 
-// Whether a matrix product of `tiles` 256 x 256 output tiles runs on them (the
-// phased kernel of tile_gemm.h) or on 64 x 64 ones.
-bool product_phased(int dt, int64_t tiles, int64_t k_bytes);
+// Whether a matrix product of rows x cols outputs (a batch of them) runs on 256
+// x tile_cols tiles (the phased kernel of tile_gemm.h; tile_cols 256, or 128
+// for the gate and up columns of a SwiGLU side by side) or on ones of 64 x
+// tile_cols / 4.
+bool product_phased(int dt, int64_t rows, int64_t cols, int tile_cols, int64_t batches,
+                    int64_t k_bytes);
 
 // ---- library-owned scratch (noalloc.hip) ---------------------------------
 // lookme_inject_noalloc keeps the criticality keys of up to

@@ -661,16 +661,16 @@ __global__ __launch_bounds__(512, 2) void phase_gemm_kernel(TileGemmParams a) {
   }
 }
 
+// output columns of a phased tile (a SwiGLU's gate and up columns share it)
 template <int EPI>
-static int64_t phase_tiles(const TileGemmParams& p, int batches) {
-  using S = PgShape<4, 2>;
-  constexpr int TCOLS = EPI == EPI_SWIGLU ? S::HN : S::BN;
-  return (p.rows + S::BM - 1) / S::BM * ((p.cols + TCOLS - 1) / TCOLS) * batches;
+constexpr int phase_cols() {
+  return EPI == EPI_SWIGLU ? PgShape<4, 2>::HN : PgShape<4, 2>::BN;
 }
 
 template <int EPI>
 static hipError_t launch_phase(int dt, TileGemmParams p, int batches, hipStream_t st) {
-  const int64_t tiles = phase_tiles<EPI>(p, batches);
+  constexpr int TCOLS = phase_cols<EPI>();
+  const int64_t tiles = (p.rows + 255) / 256 * ((p.cols + TCOLS - 1) / TCOLS) * batches;
   p.batches = batches;
   const PhasePlan pl = phase_plan((int)tiles);
   // with counts the number of tiles is the device's: any number up to `tiles`
@@ -698,7 +698,8 @@ hipError_t launch_tile_gemm(int dt, TileGemmParams p, int batches, hipStream_t s
   // rows inside 4 GiB.
   const bool near = p.a_bytes < (8 << 20) && p.k_bytes < (8 << 20) && p.b_ld < (8 << 20) &&
                     (p.a_sel == nullptr || p.sel_rows * p.a_bytes < ((int64_t)1 << 32));
-  if (p.cols % 8 == 0 && near && product_phased(dt, phase_tiles<EPI>(p, batches), p.k_bytes))
+  if (p.cols % 8 == 0 && near &&
+      product_phased(dt, p.rows, p.cols, phase_cols<EPI>(), batches, p.k_bytes))
     return launch_phase<EPI>(dt, p, batches, st);
   if constexpr (EPI != EPI_SWIGLU) {
     // 32-row tiles while every one has a CU of its own and 64-row ones leave

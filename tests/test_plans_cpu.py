@@ -26,11 +26,12 @@ def route_plan(dt, rows, S, row_bytes, cos=False):
     return f(dt, rows, S, row_bytes, cos)
 
 
-def product_phased(dt, tiles, k_bytes):
-    f = lk.load()._ZN6lookme14product_phasedEill
-    f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64]
+def product_phased(dt, rows, cols, k_bytes, batches=1, tile_cols=256):
+    f = lk.load()._ZN6lookme14product_phasedEillill
+    f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64,
+                  ctypes.c_int64]
     f.restype = ctypes.c_bool
-    return f(dt, tiles, k_bytes)
+    return f(dt, rows, cols, tile_cols, batches, k_bytes)
 
 
 @pytest.mark.parametrize("dt,rows,S,row_bytes,mode", [
@@ -108,14 +109,31 @@ def test_a_workspace_serves_every_smaller_batch(dt, S, key_bytes, score):
 @pytest.mark.parametrize("dt,tiles,k_bytes,phased", [
     (BF16, 47, 4096, False), (BF16, 48, 4096, True), (BF16, 128, 1024, False),
     (BF16, 129, 1024, True),
-    # float32: where the rounds are nearly full (a round of 256 tiles took
-    # 13% less than the same on 64 x 64 tiles)
-    (F32, 128, 8192, False), (F32, 200, 8192, False), (F32, 225, 8192, True),
+    # float32: where the rounds, of whole tiles or of quarters, are nearly full
+    (F32, 48, 8192, False), (F32, 50, 8192, True), (F32, 64, 8192, True), (F32, 90, 8192, False),
+    (F32, 128, 8192, True), (F32, 190, 8192, False), (F32, 225, 8192, True),
     (F32, 256, 2048, True), (F32, 300, 8192, True), (F32, 385, 8192, False),
     (F32, 450, 8192, True), (F32, 512, 4096, True), (F32, 5000, 4096, True),
 ])
 def test_products_on_large_tiles(dt, tiles, k_bytes, phased):
-    assert product_phased(dt, tiles, k_bytes) == phased
+    assert product_phased(dt, 256 * tiles, 256, k_bytes) == phased
+    assert product_phased(dt, 256, 256, k_bytes, batches=tiles) == phased
+    assert product_phased(dt, 256, 128 * tiles, k_bytes, tile_cols=128) == phased
+
+
+@pytest.mark.parametrize("dt,rows,cols,k_bytes,batches,tile_cols", [
+    # one column tile, a quarter or half of it padding: two to three times the
+    # time of 64 x 64 tiles
+    (F32, 131072, 64, 4096, 1, 256), (F32, 131072, 128, 4096, 1, 256),
+    (BF16, 33000, 64, 4096, 1, 256), (BF16, 16385, 128, 8192, 1, 256),
+    # a row block of 1 or 44 rows in each of four layers
+    (F32, 257, 4096, 8192, 4, 128), (F32, 300, 4096, 8192, 4, 128),
+    (BF16, 300, 1600, 2304, 4, 128), (BF16, 600, 1600, 2304, 2, 128),
+    # both edges, short sums
+    (BF16, 12000, 640, 256, 1, 256), (BF16, 16385, 384, 1024, 1, 256),
+])
+def test_products_mostly_of_padding_on_small_tiles(dt, rows, cols, k_bytes, batches, tile_cols):
+    assert not product_phased(dt, rows, cols, k_bytes, batches, tile_cols)
 
 
 def relevance_ranges(rows, P, k):
