@@ -14,6 +14,9 @@ namespace lookme {
 // ---- projection: q[l, t, :] = round(x[t, :] . Wt[l]^T) --------------------
 hipError_t launch_project(int dt, const void* x, const void* wt, void* q, int64_t n, int d_in,
                           int d_e, int layers, hipStream_t st);
+// Whether an n x cols projection runs on project_round_kernel, one round of 256
+// x 256 tiles.
+bool project_one_round(int dt, int64_t n, int64_t cols, int64_t k_bytes);
 
 // Whether a matrix product of rows x cols outputs (a batch of them) runs on 256
 // x tile_cols tiles (the phased kernel of tile_gemm.h; tile_cols 256, or 128

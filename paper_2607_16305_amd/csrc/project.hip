@@ -316,25 +316,36 @@ static void launch_tiles(const void* x, const void* wt, void* q, int64_t n, int 
                      static_cast<char*>(q), n, N, kb, d_e, (int)tiles);
 }
 
+// One nearly full round of large tiles leaves no CU to the norms and the
+// select of a second stream, which then hold up the routing: beside them the
+// phased kernel, whose tiles fill a CU's registers, made the step of 32768
+// rows 2.235 ms, its 128 x 256 tiles in two rounds 2.169 (projection 150 us),
+// project_round_kernel 2.147 (134 us).  Alone: 32768 x 512 x 4096 113 us
+// phased, 122 here; 32768 x 512 x 2048 69.5 us on 128 x 256 tiles, 64.6 here;
+// float32 616 us on 64 x 64 tiles, 567 here.  bf16 sums of at most 1 KiB of
+// K are over before the phased pipeline is full, so half a round is enough
+// for it there (5000 x 2048 x 512 26.9 us phased, 25.5 here; 16384 x 512 x
+// 512 25.7 us on 64 x 64 tiles, 24.9 here).
+// Tiles that are mostly padding leave that to the 64 x 64 ones (on those and
+// here: float32 65536 x 64 x 2048 166 us and 521, x 192 466 and 521, 16384 x
+// 896 540 and 519; bf16 32768 x 64 x 512 13.5 and 23.3, 16384 x 320 x 512
+// 20.7 and 24.0, 8192 x 896 x 512 24.6 and 28.4).
+bool project_one_round(int dt, int64_t n, int64_t cols, int64_t k_bytes) {
+  const int64_t large = ((n + 255) / 256) * ((cols + 255) / 256);
+  const int64_t filled = ((n + 63) / 64) * ((cols + 63) / 64) / 16;
+  const bool brief = dt == DT_BF16 && k_bytes <= 1024;
+  return k_bytes % PR_KB == 0 && large <= 256 && large > (brief ? 127 : 224) &&
+         filled > (dt != DT_BF16 ? 200 : brief && large == 128 ? 112 : 100);
+}
+
 hipError_t launch_project(int dt, const void* x, const void* wt, void* q, int64_t n, int d_in,
                           int d_e, int layers, hipStream_t st) {
   if (n == 0) return hipSuccess;
   const int es = dt == DT_BF16 ? 2 : 4;
   const int N = layers * d_e;
   const int64_t kb = (int64_t)d_in * es;
-  // One nearly full round of large tiles leaves no CU to the norms and the
-  // select of a second stream, which then hold up the routing: beside them the
-  // phased kernel, whose tiles fill a CU's registers, made the step of 32768
-  // rows 2.235 ms, its 128 x 256 tiles in two rounds 2.169 (projection 150 us),
-  // project_round_kernel 2.147 (134 us).  Alone: 32768 x 512 x 4096 113 us
-  // phased, 122 here; 32768 x 512 x 2048 69.5 us on 128 x 256 tiles, 64.6 here;
-  // float32 616 us on 64 x 64 tiles, 567 here.  bf16 sums of at most 1 KiB of
-  // K are over before the phased pipeline is full, so half a round is enough
-  // for it there (5000 x 2048 x 512 26.9 us phased, 25.5 here; 16384 x 512 x
-  // 512 25.7 us on 64 x 64 tiles, 24.9 here).
-  const int64_t large = ((n + 255) / 256) * ((N + 255) / 256);
-  if (kb % PR_KB == 0 && large <= 256 &&
-      large > (dt == DT_BF16 && kb <= 1024 ? 127 : 224)) {
+  if (project_one_round(dt, n, N, kb)) {
+    const int64_t large = ((n + 255) / 256) * ((N + 255) / 256);
     if (dt == DT_BF16) launch_round<DT_BF16>(x, wt, q, n, N, kb, d_e, (int)large, st);
     else launch_round<DT_F32>(x, wt, q, n, N, kb, d_e, (int)large, st);
     return hipGetLastError();

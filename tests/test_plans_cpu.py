@@ -1,7 +1,8 @@
 """The rules that choose a kernel by size, called in the built library (they
 are host code; no GPU is used): routing in the scoring kernel's shared mode or
-in the tile kernel, the partials that its splits need, the products that
-run on 256 x 256 tiles, and the ranges of the relevance MLP's second layer."""
+in the tile kernel, the partials that its splits need, the products and the
+projections that run on 256 x 256 tiles, and the ranges of the relevance MLP's
+second layer."""
 
 import ctypes
 
@@ -134,6 +135,26 @@ def test_products_on_large_tiles(dt, tiles, k_bytes, phased):
 ])
 def test_products_mostly_of_padding_on_small_tiles(dt, rows, cols, k_bytes, batches, tile_cols):
     assert not product_phased(dt, rows, cols, k_bytes, batches, tile_cols)
+
+
+@pytest.mark.parametrize("dt,n,cols,k_bytes,one_round", [
+    (BF16, 32768, 512, 8192, True), (BF16, 8192, 2048, 1024, True), (BF16, 16384, 512, 1024, True),
+    (BF16, 23040, 512, 1024, True), (F32, 16384, 896, 8192, True), (F32, 8192, 2048, 512, True),
+    # fewer tiles, or more than a round of them
+    (BF16, 23040, 512, 4096, False), (F32, 23040, 512, 4096, False),
+    (BF16, 33000, 512, 4096, False), (BF16, 16128, 512, 1024, False),
+    # mostly padding: 64 x 64 tiles take a third to nine tenths of the time
+    (F32, 65536, 64, 8192, False), (F32, 65536, 192, 8192, False), (F32, 32768, 320, 4096, False),
+    (BF16, 32768, 64, 1024, False), (BF16, 65536, 64, 8192, False), (BF16, 16384, 320, 1024, False),
+    (BF16, 8192, 896, 1024, False),
+    # no whole K stages
+    (BF16, 32768, 512, 8256, False),
+])
+def test_projections_of_one_round(dt, n, cols, k_bytes, one_round):
+    f = lk.load()._ZN6lookme17project_one_roundEilll
+    f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int64]
+    f.restype = ctypes.c_bool
+    assert f(dt, n, cols, k_bytes) == one_round
 
 
 def relevance_ranges(rows, P, k):
