@@ -172,7 +172,8 @@ __global__ __launch_bounds__(INJ_THREADS) void inject_kernel(
 constexpr int MS_GROUP = 256;              // threads of a scale at most
 constexpr int64_t MS_WIDE = 327680, MS_NARROW = 393216;   // threads of a launch
 constexpr int64_t MS_CU_LDS = 160 * 1024, MS_CU_THREADS = 1280;
-constexpr int MS_ROW_THREADS = 1024;       // threads of a row at most
+// threads of a row at most (k > 16 holds more loads in registers)
+constexpr int ms_row_threads(int k) { return k > 16 ? 512 : 1024; }
 
 template <int DT, int K>
 __device__ __forceinline__ u32x4_t weighted_chunk(const char* __restrict__ values,
@@ -225,7 +226,7 @@ __device__ __forceinline__ float chunk_dot(u32x4_t a, u32x4_t b, float acc) {
 // token id is out of range is left alone and counted once a scale; a scale
 // whose scene or a primitive is out of range has R^m = 0 and is counted.
 template <int DT, int K>
-__global__ __launch_bounds__(MS_ROW_THREADS) void ms_mix_kernel(
+__global__ __launch_bounds__(ms_row_threads(K)) void ms_mix_kernel(
     int64_t n, const int32_t* __restrict__ kept, const int32_t* __restrict__ scene_all,
     const int32_t* __restrict__ prim_all, const float* __restrict__ w_all,
     const char* __restrict__ values, int Sm, int P, int k, int M, int64_t v_bytes,
@@ -353,7 +354,7 @@ hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const in
   const int64_t fill = MS_CU_LDS / (scales * vb + 256) * gs < MS_CU_THREADS ? 2 : 1;
   int64_t groups = room > fill ? room : fill;
   if (groups > scales) groups = scales;
-  if (groups > MS_ROW_THREADS / gs) groups = MS_ROW_THREADS / gs;
+  if (groups > ms_row_threads(k) / gs) groups = ms_row_threads(k) / gs;
   const int64_t turns = (scales + groups - 1) / groups;
   groups = (scales + turns - 1) / turns;   // as even as the turns allow
   const float inv_sqrt_d = 1.0f / sqrtf((float)d_v);
@@ -366,7 +367,8 @@ hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const in
   };
   if (dt != DT_BF16) launch(ms_mix_kernel<DT_F32, 8>);
   else if (k <= 8) launch(ms_mix_kernel<DT_BF16, 8>);
-  else launch(ms_mix_kernel<DT_BF16, 16>);
+  else if (k <= 16) launch(ms_mix_kernel<DT_BF16, 16>);
+  else launch(ms_mix_kernel<DT_BF16, 32>);
   return hipGetLastError();
 }
 

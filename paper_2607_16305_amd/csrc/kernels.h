@@ -212,12 +212,15 @@ constexpr int MS_LDS_BYTES = 60 * 1024;   // the R^m of a row that the mix keeps
 // saves R's way through memory, and wins wherever its k value rows in
 // registers and the R^m in LDS leave enough waves a CU: up to 8 picks always
 // (bf16 8 x 3584: 11520 rows 1013 -> 952 us, 2 x 512: 56.1 -> 49.3), up to 16
-// in bf16 on few rows of few scales (4 x 2048: 1500 rows 86.3 -> 83.7, 11520
-// 473 -> 496; 8 x 2048 1500 rows 137 -> 141; float32 2 x 1024 77.1 -> 91.8),
-// with more not (4 x 2048, k = 32: 1500 rows 141 -> 173).
+// in bf16 on few rows (4 x 2048: 1500 rows 86.3 -> 83.7, 11520 473 -> 496; 8 x
+// 512: 255 rows 24.1 -> 16.5, 2500 56.6 -> 62.0; float32 2 x 1024 77.1 -> 91.8),
+// with more in bf16 on few narrow ones (k = 32, 2 x 1024: 255 rows 25 -> 21, 600
+// 32 -> 37; 8 x 1536: 20 rows 27 -> 51; 4 x 2048: 1500 rows 141 -> 173).
 inline bool ms_gathers(bool f32, int scales, int64_t row_bytes, int k, int64_t rows) {
   if (scales * row_bytes > MS_LDS_BYTES) return true;
-  return k > 8 && (f32 || k > 16 || scales > 4 || rows >= 4096);
+  if (f32 || k <= 8) return k > 8;
+  if (k > 16 && scales * row_bytes > 8192) return true;
+  return rows >= (k > 16 || scales > 4 ? 512 : 4096);
 }
 hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const int32_t* kept,
                          const int32_t* scene, const int32_t* prim, const float* w,

@@ -307,9 +307,12 @@ def test_multiscale_entry_points_validate(lib):
         wide = lk.lookme_create(_desc(dtype=lk.LOOKME_BF16, key_dim=512, value_dim=2048,
                                       prims_per_scene=1024, top_k=32, num_scenes=256), FAKE,
                                 FAKE, FAKE)
-        try:   # 32 picks: the rows are gathered into the workspace first
+        try:   # 32 picks: from 512 rows on they are gathered into the workspace first
+            few, many = (lk.lookme_workspace_size(wide, 1, n) for n in (511, 512))
             assert S(lambda: lk.lookme_set_multiscale(wide, 2, 2048, FAKE)) == lk.LOOKME_OK
-            assert lk.lookme_workspace_size(wide, 1, 100) >= base + 3 * queries
+            row = 2048 * 2
+            assert 511 * row <= lk.lookme_workspace_size(wide, 1, 511) - few < 2 * 511 * row
+            assert 3 * 512 * row <= lk.lookme_workspace_size(wide, 1, 512) - many
         finally:
             lk.lookme_destroy(wide)
         assert S(lambda: call(d_h=4096)) == lk.LOOKME_ERR_INVALID

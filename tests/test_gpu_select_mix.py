@@ -128,7 +128,9 @@ def test_gate_lists_the_open_rows(n):
 @pytest.mark.parametrize("dtype,d_v,scales,k", [("bf16", 64, 1, 4), ("bf16", 2112, 3, 7),
                                                 ("bf16", 4160, 2, 12), ("f32", 1056, 5, 17),
                                                 ("f32", 2080, 8, 3), ("bf16", 3584, 8, 8),
-                                                ("bf16", 576, 7, 8), ("f32", 1920, 8, 5)])
+                                                ("bf16", 576, 7, 8), ("f32", 1920, 8, 5),
+                                                ("bf16", 512, 8, 16), ("bf16", 1344, 3, 24),
+                                                ("bf16", 2048, 2, 20), ("bf16", 2112, 2, 24)])
 def test_multiscale_mix_against_float64(dtype, d_v, scales, k):
     """H + sum_m alpha_m R^m from the library's own picks.  bf16: the stored
     value's rounding (2^-9 of it), an R^m that rounds the other way (2^-8 of
