@@ -350,7 +350,9 @@ hipError_t launch_ms_mix(int dt, int scales, int64_t n, int64_t n_keep, const in
   const int64_t es = dt == DT_BF16 ? 2 : 4, vb = (int64_t)d_v * es;
   const int ch = (int)(vb / 16);
   const int gs = ch >= MS_GROUP ? MS_GROUP : (ch + 63) / 64 * 64;
-  const int64_t room = (gs < MS_GROUP ? MS_NARROW : MS_WIDE) / (n_keep * gs);
+  // a counted list has room for every row; about half of a gate is open
+  const int64_t rows = count != nullptr ? (n_keep + 1) / 2 : n_keep;
+  const int64_t room = (gs < MS_GROUP ? MS_NARROW : MS_WIDE) / (rows * gs);
   const int64_t fill = MS_CU_LDS / (scales * vb + 256) * gs < MS_CU_THREADS ? 2 : 1;
   int64_t groups = room > fill ? room : fill;
   if (groups > scales) groups = scales;
